@@ -312,7 +312,8 @@ size_t exfold_calibrate_workspace_size(const exfold_layer *layer, int64_t m, int
  *   x_cal [m, d] calibration tokens.  COROUTED: u = E_s(x), v = E_t(x) for the
  *   ordered pairs s != t of each token's Top-K experts; COMMON: for all pairs.
  *   Per pair, with w = ||u||_2: A = sum w<u,v>, V = sum w||v||^2,
- *   C = sum w||u||^2, n = count (float64, token order).
+ *   C = sum w||u||^2, n = count (float64; runs of s's tokens in token order, the
+ *   runs added in order).
  *   S[s,t] = A/(V+lambda) (0 if n == 0 or V+lambda == 0), clipped to
  *   [-clip, clip] when clip > 0; L[s,t] = max(0, C - 2 S A + S^2 V)/(C + 1e-12)
  *   with the clipped S, 1e30 when n == 0; S[s,s] = 1, L[s,s] = 0.

@@ -267,7 +267,7 @@ exfold_status plan_execute(const exfold_layer *L, int64_t T, int64_t k_out, Exec
 struct CalibPlan {
   int m = 0, N = 0, K = 0, kr = 0, P = 1;
   size_t o_logits = 0, o_topk_ids = 0, o_topk_w = 0, o_route_ids = 0, o_route_w = 0, o_pos = 0,
-         o_gram = 0;
+         o_gram = 0, o_part = 0;
   ExecPlan ex;
   size_t total = 0;
 };
@@ -293,6 +293,7 @@ exfold_status plan_calibrate(const exfold_layer *L, int64_t m, int32_t mode, Cal
   p.o_pos = c.take(sizeof(int16_t) * (size_t)p.m * p.N);
   p.o_gram = c.take(sizeof(double) * (size_t)p.m * p.kr * p.kr);
   plan_exec(L, EXFOLD_PHASE_PREFILL, p.m, p.kr, false, true, p.N, c, p.ex);
+  p.o_part = c.take(sizeof(double) * calib_partial_doubles(p.ex.R, p.N, p.ex.gu.bm));
   p.total = c.off;
   return EXFOLD_OK;
 }
@@ -678,8 +679,8 @@ exfold_status exfold_calibrate_projectors(const exfold_layer *layer, const void 
                           (int)layer->d, gram, s) != hipSuccess)
       return EXFOLD_ERR_DEVICE;
   }
-  if (launch_calib_finalize(gram, pos, p.m, p.N, p.kr, lambda, clip, S, L, h, pair_stats, s) !=
-      hipSuccess)
+  if (launch_calib_finalize(gram, pos, perm_buffers(p.ex, ws, nullptr, nullptr), p.ex.gu.bm, p.m, p.N, p.kr,
+                            lambda, clip, at<double>(ws, p.o_part), S, L, h, pair_stats, s) != hipSuccess)
     return EXFOLD_ERR_DEVICE;
   return EXFOLD_OK;
 }
