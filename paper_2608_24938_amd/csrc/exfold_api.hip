@@ -531,7 +531,7 @@ exfold_status forward_impl(const exfold_layer *layer, const exfold_tables *table
   float *fold_w = dbg.fold_w ? dbg.fold_w : at<float>(ws, p.o_fold_w);
 
   record(dbg.events, EXFOLD_EV_START, s);
-  // few experts (bf16): the router logits are computed inside the routing
+  // few experts: the router logits are computed inside the routing
   // kernel (one workgroup per token), so the router stage takes no launch
   const bool small = route_small_fits(layer->dtype, p.N, p.T);
   if (!small && launch_router_logits(layer->dtype, x, layer->w_router, p.T, p.N, (int)layer->d, p.P, part,
@@ -547,7 +547,7 @@ exfold_status forward_impl(const exfold_layer *layer, const exfold_tables *table
                    float *fw, float cap, int flags, int32_t *oms = nullptr, float *omw = nullptr,
                    int32_t *omq = nullptr, float *wret = nullptr) {
     if (small)
-      return launch_route_small(x, layer->w_router, (int)layer->d, bias, dbg.logits, p.T, p.N, p.K, kp, h, S, L,
+      return launch_route_small(layer->dtype, x, layer->w_router, (int)layer->d, bias, dbg.logits, p.T, p.N, p.K, kp, h, S, L,
                                 topk_ids, topk_w, keep_out, fi, fw, s, cap, flags, oms, omw, omq, wret);
     return launch_route_tokens(part, p.P, bias, dbg.logits, p.T, p.N, p.K, kp, h, S, L, topk_ids, topk_w,
                                keep_out, nullptr, fi, fw, s, cap, flags, oms, omw, omq, wret);

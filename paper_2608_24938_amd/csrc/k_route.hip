@@ -22,7 +22,8 @@ namespace exfold {
 // token groups) and add their partial sums in a fixed order through LDS.  Many
 // tokens: one block covers every expert (W_r is read once per 16*TT tokens); few tokens: 16 experts per block and the d axis split
 // over the grid, so the small GEMM still spreads over the CUs.
-// f32: one thread per logit.
+// f32: workgroups of 16 tokens x 16 experts on 16x16x4 MFMAs, the four waves
+// splitting d (see the float32 expert GEMM for the operand layout).
 // ---------------------------------------------------------------------------
 template <int NT, int KS, int TT = 1>
 __global__ __launch_bounds__(64 * KS) void router_logits_bf16(const bf16_t *__restrict__ x,
@@ -253,17 +254,34 @@ static void launch_router_wide(const bf16_t *x, const bf16_t *wr, int T, int N, 
     router_logits_bf16<NT, 4><<<dim3(blocks, 1, 1), 256, 0, s>>>(x, wr, T, N, d, d, part);
 }
 
+// One thread a logit walked d alone (64 tokens, 8 experts, d 256: 21 us, in two workgroups).
 __global__ __launch_bounds__(256) void router_logits_f32(const float *__restrict__ x,
                                                          const float *__restrict__ wr, int T,
                                                          int N, int d, float *__restrict__ part) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= T * N) return;
-  const int t = idx / N, e = idx % N;
-  const float *xr = x + (size_t)t * d;
-  const float *wrow = wr + (size_t)e * d;
-  float acc = 0.f;
-  for (int k = 0; k < d; ++k) acc = fmaf(xr[k], wrow[k], acc);
-  part[idx] = acc;
+  __shared__ float red[4][256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16, kq = (lane >> 4) * 4;
+  const float *xr = x + (size_t)min(t0 + (lane & 15), T - 1) * d + kq;
+  const float *wrow = wr + (size_t)min(e0 + (lane & 15), N - 1) * d + kq;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const int span = d / 4;  // d % 128 == 0: whole steps of 32 columns
+  for (int k = wave * span; k < (wave + 1) * span; k += 32) {
+    f32x4 a[2], b[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      a[u] = *reinterpret_cast<const f32x4 *>(xr + k + 16 * u);
+      b[u] = *reinterpret_cast<const f32x4 *>(wrow + k + 16 * u);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][r * 64 + lane] = acc[r];
+  __syncthreads();
+  const int i = threadIdx.x, t = t0 + (lane >> 4) * 4 + wave, e = e0 + (lane & 15);
+  if (t < T && e < N) part[(size_t)t * N + e] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
 }
 
 hipError_t launch_router_logits(int dtype, const void *x, const void *w_router, int T, int N, int d,
@@ -296,7 +314,7 @@ hipError_t launch_router_logits(int dtype, const void *x, const void *w_router, 
       else launch_router_wide<16>(xb, wb, T, N, d, part, s);
     }
   } else {
-    router_logits_f32<<<(T * N + 255) / 256, 256, 0, s>>>(
+    router_logits_f32<<<dim3((T + 15) / 16, (N + 15) / 16), 256, 0, s>>>(
         static_cast<const float *>(x), static_cast<const float *>(w_router), T, N, d, part);
   }
   return hipGetLastError();
@@ -563,17 +581,30 @@ __global__ __launch_bounds__(256) void route_tokens_kernel(const float *__restri
   route_token_wave(a, t, lane, part != nullptr, v, hv);
 }
 
-// Routers of at most 32 experts (bf16): one workgroup per token computes its N
+// Routers of at most 32 experts: one workgroup per token computes its N
 // logits (each thread a 16-byte slice of d per step against every expert,
 // then a fixed-order tree: DPP inside each wave, the four waves in order)
 // and wave 0 routes the token as route_tokens_kernel does.  One launch
 // replaces the router and Top-K kernels; W_r (<= 32 d elements) stays in L2.
 constexpr int kRouteSmallMaxT = 1024;  // route_small_kernel: one workgroup per token up to this batch
 
-template <int NM>
-__global__ __launch_bounds__(256) void route_small_kernel(const bf16_t *__restrict__ x,
-                                                         const bf16_t *__restrict__ wr, int d,
-                                                         const float *__restrict__ bias,
+// The elements of a 16-byte piece, as float32.
+template <typename E>
+__device__ __forceinline__ void unpack16(const u32x4 &u, float (&f)[16 / sizeof(E)]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if constexpr (sizeof(E) == 2) {
+      f[2 * q] = __uint_as_float(u[q] << 16);
+      f[2 * q + 1] = __uint_as_float(u[q] & 0xffff0000u);
+    } else {
+      f[q] = __uint_as_float(u[q]);
+    }
+  }
+}
+
+template <typename E, int NM>
+__global__ __launch_bounds__(256) void route_small_kernel(const E *__restrict__ x, const E *__restrict__ wr,
+                                                         int d, const float *__restrict__ bias,
                                                          float *__restrict__ logits_out, const RouteArgs a) {
   __shared__ float red[4][NM];
   const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -583,14 +614,15 @@ __global__ __launch_bounds__(256) void route_small_kernel(const bf16_t *__restri
   float acc[NM];
 #pragma unroll
   for (int e = 0; e < NM; ++e) acc[e] = 0.f;
-  const bf16_t *xr = x + (size_t)t * d;
+  const E *xr = x + (size_t)t * d;
+  constexpr int kV = 16 / sizeof(E);
   // two 16-byte steps of d per round, every load of the round issued first
   constexpr int kU = NM <= 8 ? 2 : 1;
-  for (int k0 = tid * 8; k0 < d; k0 += kU * 256 * 8) {
+  for (int k0 = tid * kV; k0 < d; k0 += kU * 256 * kV) {
     u32x4 xu[kU], wu[kU][NM];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * 256 * 8;
+      const int k = k0 + u * 256 * kV;
       if (k < d) {
         xu[u] = *reinterpret_cast<const u32x4 *>(xr + k);
 #pragma unroll
@@ -600,21 +632,16 @@ __global__ __launch_bounds__(256) void route_small_kernel(const bf16_t *__restri
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      if (k0 + u * 256 * 8 >= d) break;
-      float xf[8];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        xf[2 * q] = __uint_as_float(xu[u][q] << 16);
-        xf[2 * q + 1] = __uint_as_float(xu[u][q] & 0xffff0000u);
-      }
+      if (k0 + u * 256 * kV >= d) break;
+      float xf[kV];
+      unpack16<E>(xu[u], xf);
 #pragma unroll
       for (int e = 0; e < NM; ++e)
         if (e < N) {
+          float wf[kV];
+          unpack16<E>(wu[u][e], wf);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            acc[e] = fmaf(xf[2 * q], __uint_as_float(wu[u][e][q] << 16), acc[e]);
-            acc[e] = fmaf(xf[2 * q + 1], __uint_as_float(wu[u][e][q] & 0xffff0000u), acc[e]);
-          }
+          for (int q = 0; q < kV; ++q) acc[e] = fmaf(xf[q], wf[q], acc[e]);
         }
     }
   }
@@ -634,6 +661,15 @@ __global__ __launch_bounds__(256) void route_small_kernel(const bf16_t *__restri
     if (logits_out) logits_out[(size_t)t * N + lane] = l;
   }
   route_token_wave(a, t, lane, true, v, hv);
+}
+
+template <typename E>
+static void launch_route_small_t(const void *x, const void *w_router, int d, const float *bias,
+                                 float *logits_out, const RouteArgs &a, hipStream_t s) {
+  const E *xe = static_cast<const E *>(x), *we = static_cast<const E *>(w_router);
+  if (a.N <= 8) route_small_kernel<E, 8><<<a.T, 256, 0, s>>>(xe, we, d, bias, logits_out, a);
+  else if (a.N <= 16) route_small_kernel<E, 16><<<a.T, 256, 0, s>>>(xe, we, d, bias, logits_out, a);
+  else route_small_kernel<E, 32><<<a.T, 256, 0, s>>>(xe, we, d, bias, logits_out, a);
 }
 
 // Up to about a thousand tokens: beyond that, the per-token reads of W_r cost
@@ -728,9 +764,11 @@ __global__ __launch_bounds__(64 * KS) void route_block_kernel(const bf16_t *__re
   }
 }
 
-bool route_small_fits(int dtype, int N, int T) { return dtype == EXFOLD_BF16 && N <= 32; }
+bool route_small_fits(int dtype, int N, int T) {
+  return N <= 32 && (dtype == EXFOLD_BF16 || T <= kRouteSmallMaxT);
+}
 
-hipError_t launch_route_small(const void *x, const void *w_router, int d, const float *bias,
+hipError_t launch_route_small(int dtype, const void *x, const void *w_router, int d, const float *bias,
                               float *logits_out, int T, int N, int K, int k_pre, const float *h,
                               const float *S, const float *L, int32_t *topk_ids, float *topk_w,
                               uint8_t *keep, int32_t *fold_ids, float *fold_w, hipStream_t s,
@@ -739,16 +777,15 @@ hipError_t launch_route_small(const void *x, const void *w_router, int d, const 
   if (T <= 0) return hipSuccess;
   const RouteArgs a{T, N, K, k_pre, h, S, L, topk_ids, topk_w, keep, nullptr, fold_ids, fold_w,
                     loss_cap, flags, om_src, om_w, om_q, wret};
-  const bf16_t *xb = static_cast<const bf16_t *>(x), *wb = static_cast<const bf16_t *>(w_router);
   if (T > kRouteSmallMaxT) {
+    const bf16_t *xb = static_cast<const bf16_t *>(x), *wb = static_cast<const bf16_t *>(w_router);
     const int blocks = (T + 15) / 16;
     // sixteen waves: one token each to route (eight waves routing two each: 19.4 against 16.0 us
     // for the Mixtral-shaped prefill's 4096 tokens)
     if (N <= 16) route_block_kernel<1, 16><<<blocks, 1024, 0, s>>>(xb, wb, d, bias, logits_out, a);
     else route_block_kernel<2, 16><<<blocks, 1024, 0, s>>>(xb, wb, d, bias, logits_out, a);
-  } else if (N <= 8) route_small_kernel<8><<<T, 256, 0, s>>>(xb, wb, d, bias, logits_out, a);
-  else if (N <= 16) route_small_kernel<16><<<T, 256, 0, s>>>(xb, wb, d, bias, logits_out, a);
-  else route_small_kernel<32><<<T, 256, 0, s>>>(xb, wb, d, bias, logits_out, a);
+  } else if (dtype == EXFOLD_BF16) launch_route_small_t<bf16_t>(x, w_router, d, bias, logits_out, a, s);
+  else launch_route_small_t<float>(x, w_router, d, bias, logits_out, a, s);
   return hipGetLastError();
 }
 

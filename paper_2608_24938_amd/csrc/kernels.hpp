@@ -24,10 +24,10 @@ hipError_t launch_route_tokens(const float *part, int P, const float *bias, floa
                                int32_t *om_src = nullptr, float *om_w = nullptr,
                                int32_t *om_q = nullptr, float *wret = nullptr);
 // Router logits and the per-token steps of launch_route_tokens in one kernel, for
-// bf16 layers of at most 32 experts (route_small_fits): one workgroup per token
-// up to 1024 tokens, one per 16 tokens beyond; x [T, d], w_router [N, d].
+// layers of at most 32 experts (route_small_fits): one workgroup per token up to
+// 1024 tokens, one per 16 tokens beyond (bf16 only); x [T, d], w_router [N, d].
 bool route_small_fits(int dtype, int N, int T);
-hipError_t launch_route_small(const void *x, const void *w_router, int d, const float *bias,
+hipError_t launch_route_small(int dtype, const void *x, const void *w_router, int d, const float *bias,
                               float *logits_out, int T, int N, int K, int k_pre, const float *h,
                               const float *S, const float *L, int32_t *topk_ids, float *topk_w,
                               uint8_t *keep, int32_t *fold_ids, float *fold_w, hipStream_t s,
@@ -97,7 +97,7 @@ hipError_t launch_static_pool(const float *h, int N, int D, const float *S, cons
                               hipStream_t s);
 
 // ---- expert GEMMs and combine (k_gemm.hip) ----
-// kGemmTile: 128x128 tiles; kGemmSkinny: 32x64 tiles for few rows per expert;
+// kGemmSimt: float32 layers (16 to 64 rows x 16 or 32 columns); kGemmTile: 128x128 tiles; kGemmSkinny: 32x64 tiles for few rows per expert;
 // kGemmWide: 256x256 tiles (eight waves, loads straight into LDS) in rounds of
 // `wgs` workgroups, a short last round split along the reduction.
 enum { kGemmSimt = 0, kGemmTile = 1, kGemmSkinny = 2, kGemmWide = 3 };
@@ -106,7 +106,7 @@ struct GemmPlan {
                // (output columns, or weight rows for gate/up)
   int ksplit;  // splits of the reduction (down projection only; partial outputs)
   int grid;    // workgroups launched (an upper bound on the device-side tile count)
-  int kind;    // kGemmSimt (float32 layers), kGemmTile, kGemmSkinny or kGemmWide (bf16 MFMA tiles)
+  int kind;    // kGemmSimt (float32 MFMA tiles), kGemmTile, kGemmSkinny or kGemmWide (bf16 MFMA tiles)
   int wgs;     // kGemmWide: workgroups per round (one per CU)
 };
 struct ExpertArgs {

@@ -9,7 +9,7 @@ from oracle import exfold_oracle as O
 from paper_2608_24938_amd import exfold as X
 from paper_2608_24938_amd import synth
 
-from .gpu_common import LayerPair, sync, to_dev
+from .gpu_common import TOL_Y, LayerPair, from_dev, logits_bound, per_token_rel_l2, sync, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +47,54 @@ def test_calibration_at_tile_edges(n, k, m, mode):
     np.testing.assert_array_equal(L.cpu().numpy()[~obs], rL[~obs])
     np.testing.assert_allclose(L.cpu().numpy()[obs], rL[obs], rtol=tol, atol=tol)
     np.testing.assert_allclose(h.cpu().numpy(), rh, rtol=tol)
+
+
+def _execute(shape, T, ids, seed):
+    """moe_execute on given routes against the oracle: the largest per-token error."""
+    lp = LayerPair(shape, seed=seed)
+    rng = np.random.default_rng(seed)
+    w = rng.standard_normal(ids.shape).astype(np.float32)
+    xs = synth.tokens(shape, T, seed=seed)
+    print(f"execute: {shape.dtype} d={shape.d} I={shape.inter} N={shape.n_experts} routes={ids.shape}", flush=True)
+    y = X.moe_execute(lp.dev, to_dev(xs), to_dev(ids), to_dev(w))
+    sync()
+    ref = O.moe_output(lp.ref, synth.widen(xs), ids, w)
+    return per_token_rel_l2(from_dev(y), ref).max()
+
+
+def _skewed(T, k, n, seed):
+    """Route ids [T, k], half of them on expert 0 (ragged groups, some empty)."""
+    rng = np.random.default_rng(seed)
+    ids = rng.integers(0, n, size=(T, k)).astype(np.int32)
+    ids[rng.random((T, k)) < 0.5] = 0
+    return ids
+
+
+# float32 tiles of 16, 32 and 64 rows: either side of 16 and 32 rows per busy expert, one
+# row, ragged groups, the shared expert, a reduction of one step a wave (d 128, I 64) and a
+# ragged last batch of steps (d 640: ten steps a wave; I 320: five).
+@pytest.mark.parametrize("d,inter,n,k,shared,T", [(128, 64, 5, 1, 0, 1), (128, 64, 5, 2, 0, 40), (128, 64, 5, 2, 0, 41),
+                                                  (640, 320, 5, 2, 320, 79), (640, 320, 5, 2, 0, 81),
+                                                  (256, 192, 3, 1, 192, 333), (1024, 576, 8, 2, 0, 1100)])
+def test_float32_tiles(d, inter, n, k, shared, T):
+    shape = _shape(d, inter, n, k, shared=shared)
+    assert _execute(shape, T, _skewed(T, k, n, T), seed=3) <= TOL_Y["f32"]
+
+
+# float32 router: N <= 32 in the routing kernel up to 1024 tokens (8, 16 and 32 experts a
+# build), 16 x 16 tiles beyond either limit.
+@pytest.mark.parametrize("n,T,d", [(7, 1, 128), (13, 5, 1152), (32, 33, 640), (33, 17, 384), (32, 1024, 128),
+                                   (32, 1025, 128), (6, 1031, 256)])
+def test_float32_router_logits(n, T, d):
+    shape = _shape(d, 64, n, 2, bias=True)
+    lp = LayerPair(shape, seed=n)
+    xs = synth.tokens(shape, T, seed=n)
+    dbg = X.debug_buffers(lp.dev, T, "dense", 0, "cuda:0")
+    print(f"router f32: N={n} T={T} d={d}", flush=True)
+    X.moe_forward(lp.dev, to_dev(xs), "dense", debug=dbg)
+    sync()
+    got = dbg["logits"].cpu().numpy()
+    ref = O.router_logits(xs, lp.ref.w_router, lp.ref.router_bias)
+    assert np.all(np.abs(got.astype(np.float64) - ref) <= logits_bound(xs, lp.ref.w_router, lp.ref.router_bias, d))
+    r_ids, _ = O.route(got, 2)
+    np.testing.assert_array_equal(dbg["topk_ids"].cpu().numpy(), r_ids)
