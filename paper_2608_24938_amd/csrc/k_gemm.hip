@@ -326,12 +326,11 @@ __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
 
 // ---------------------------------------------------------------------------
 // Wide tile for the prefill GEMMs (many rows per retained expert): 256x256
-// macro tile, eight waves (two per SIMD), wave (wm, wn) owning tile rows
-// 128 wm .. 128 wm + 127 and 64 columns (gate/up: gate columns 32 wn .. 32 wn +
-// 31 with the matching up columns; 4x2 MFMA tiles); a group's last rows, when
-// at most 128, form a 128x512 tile over two n-tiles (the waves in one row).
-// Four waves of 128x128 each (one per SIMD, accumulators in AGPRs) measured
-// 7-11% slower.  The operands go from global memory
+// macro tile, eight waves (two per SIMD) of 4x2 MFMA tiles each (gate/up: gate
+// columns with the matching up columns); a group's last rows, when at most 128,
+// form a 128x512 tile over two n-tiles.  Four waves of 128x128 each (one per
+// SIMD, accumulators in AGPRs) measured 7-11% slower against eight waves that
+// met one barrier a stage.  The operands go from global memory
 // straight into LDS (global_load_lds_dwordx4) through a ring of reduction
 // stages: no staging registers and no LDS write instructions.  Against 128x128
 // tiles the bytes loaded per flop halve, and the weight panel a tile shares
@@ -340,7 +339,7 @@ __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
 // 64-wide stages with two ring buffers beat 32-wide stages with four or five
 // buffers (more bytes in flight, but 64-byte row pieces and twice the barriers).
 // ---------------------------------------------------------------------------
-constexpr int kWide = 256, kWideWaves = 8, kWideBK = 64, kWideStages = 2;
+constexpr int kWide = 256, kWideWaves = 8, kWideBK = 64;
 
 // LDS byte address of a shared-memory pointer (for M0).
 __device__ __forceinline__ uint32_t lds_addr(const void *ptr) {
@@ -394,189 +393,275 @@ __device__ __forceinline__ void wide_tile_at(const GemmKArgs &p, int L, TileId &
   }
 }
 
-// Slot of 16-byte chunk q in a tile row of BK bf16 (an involution in q): the
-// chunk columns that one ds_read_b128 takes from consecutive rows land in
-// distinct LDS banks.  64-byte rows: q ^ bits 2..3 of r; 128-byte rows: the
-// Gray-code swizzle of the register-staged tiles.
-template <int BK>
-__device__ __forceinline__ int wide_slot(int r, int q) {
-  if (BK == 32) return q ^ ((r >> 2) & 3);
-  return q ^ ((r ^ (r >> 1)) & 7);
-}
+// Slot of 16-byte chunk q in a 128-byte tile row (an involution in q): the
+// Gray-code swizzle of the register-staged tiles, so that the chunk columns one
+// ds_read_b128 takes from consecutive rows land in distinct LDS banks.
+__device__ __forceinline__ int wide_slot(int r, int q) { return q ^ ((r ^ (r >> 1)) & 7); }
 
-// 32x32 MFMA tiles per wave: the waves form two rows of kWideWaves / 2, each
-// wave owning 128 tile rows and 32 kWideTN of the 256 tile columns
-constexpr int kWideTM = 4, kWideTN = 16 / kWideWaves;
-constexpr int kWideBN = 32 * kWideTN * (kWideWaves / 2);  // tile columns (gate/up: weight rows)
-static_assert(kWideBN == kWide, "square wide tile");
+// 32x32 MFMA tiles per wave: four row blocks by two column blocks (tail tiles:
+// two by four, kept as [2 (pair) + row block][column of the pair])
+constexpr int kWideTM = 4, kWideTN = 2;
+constexpr int kWideBN = kWide;  // tile columns (gate/up: weight rows)
 // LDS ring: two stages of the 256 x 256 tile (128 KiB) or of the 128 x 512 tail (160 KiB)
-constexpr int kWideSmemElems = kWideStages * (kWide / 2 + 2 * kWideBN) * kWideBK;
+constexpr int kWideSmemElems = 2 * (kWide / 2 + 2 * kWideBN) * kWideBK;
 
-// Main loop of one wide tile over the reduction stages [k0, k1): zeroes acc,
-// streams the stages through the LDS ring and leaves the products in acc.
-// All waves of the workgroup call it; it ends with every load landed and a
-// barrier, so the ring may be refilled right after.  DBL: the 128 x 512 tail
-// tile (one row of NW waves) instead of 256 x 256 (two rows of NW / 2).
-// TMV: the calling wave's 32-row blocks that hold rows of the group (the
-// others are padding: their fragments are not read and their MFMAs not
-// issued, so their accumulators stay zero); the wave still loads its share of
-// every stage and takes every barrier.
-template <bool GATE_UP, int BK, int STAGES, int NW, bool DBL, int TMV>
+// Main loop of one wide tile over the reduction stages [k0, k1) of 64 columns
+// (at least two): zeroes acc and leaves the products in it.  The LDS ring holds
+// two stages in half tiles of 128 rows: A0, A1 (token rows) and B0, B1 (weight
+// rows; gate/up: the gate rows and the up rows), or, for a 128 x 512 tail tile
+// (DBL), A0 and B0 .. B3 (n-tile nt: B0, B1; nt + 1: B2, B3).  Wave (wm, wn) owns
+// rows 64 i + 32 wm .. + 31 (i = 0, 1) of every A half and rows 32 wn .. + 31 of
+// every B half: four quadrants of 64 x 32.
+//
+// A stage takes four phases, one quadrant each.  A phase reads one half tile's
+// fragments from LDS, issues the loads of half tiles ahead, meets the barrier,
+// and then runs the quadrant's MFMAs alone (each waits for its own fragments),
+// up to a second barrier.  The two waves of a SIMD (w and w + 4) run half a phase
+// apart: while one issues MFMAs back to back, the other reads fragments and
+// issues loads, so the matrix pipe waits for neither.  Full tiles take the
+// quadrants of a stage in ring buffer 0 in the order of weight halves 0 1 1 0 and
+// in buffer 1 in 1 0 0 1: the last phase of a stage then reads the next stage's
+// first weight half into registers that are already free.  Tail tiles go
+// through B0 .. B3 on two register sets, the last phase reading B3 and the next
+// B0.
+//
+// Half tiles are issued in the order they are read.  Full tiles: numbered so,
+// phase p reads tile p + 1 and issues tile p + 7 (two loads a wave) into the slot
+// that phase p - 2 read: the later waves' MFMAs of phase p - 2, and so their
+// reads, ended at a barrier before this phase began.  Before the phase's
+// barrier tile p + 2 must have landed: at most five tiles, 10 loads, stay in
+// flight; a load has six phases (1.5 stages) to land.  Tail tiles: five tiles a
+// stage on four phases (the second issues two), six or seven stay in flight.
+//
+// One barrier a stage with every wave reading, loading and multiplying at once
+// (one stage ahead) kept the MFMA pipes busy 57% of the cycles, this 72% of them
+// at 11% lower clock (the launch is held by the chip's power): 4096 rows on 8
+// Mixtral-shaped experts, 512 each, gate/up 877 -> 842 us (1143 TFLOP/s),
+// down 437 -> 415; ragged groups gain most, in their tail tiles (8192 Qwen3-shaped
+// tokens, K' = 4: 247 -> 229 and 177 -> 156 us).
+//
+// TMV: 32-row blocks of the wave that hold rows of the group (full: 2 .. 4, tail:
+// 0 .. 2; the others' fragments are not read and their MFMAs not issued).
+template <bool GATE_UP, bool DBL, int TMV>
 __device__ __forceinline__ void wide_tile_mma(const GemmKArgs &p, const TileId &t, int row0, int valid,
                                               int k0, int k1, bf16_t *smem,
                                               f32x16 (&acc)[kWideTM][kWideTN]) {
-  // NW waves in WM rows of WN; each wave owns 128 rows and 32 TN columns
-  // (gate/up: 16 TN gate + the matching 16 TN up columns)
-  constexpr int WM = DBL ? 1 : 2, WN = NW / WM;
-  constexpr int BM = 128 * WM, TM = kWideTM, TN = kWideTN, BN = 32 * TN * WN;
-  static_assert(NW == kWideWaves, "accumulator shape");
-  static_assert(TMV >= 0 && TMV <= TM, "valid row blocks");
-  constexpr int STAGE = (BM + BN) * BK;          // elements of one stage (A rows, then B rows)
-  constexpr int CPR = BK / 8;                    // 16-byte chunks per row
-  constexpr int RPB = 64 / CPR;                  // rows per 1 KiB block
-  constexpr int BLOCKS = (BM + BN) / RPB;        // blocks per stage
-  constexpr int PW = BLOCKS / NW;                // DMA loads per wave per stage
-  constexpr int AHEAD = STAGES - 1;              // stages in flight while one is computed
-  constexpr int VMC = (AHEAD - 1) * PW;          // loads allowed in flight at a stage's wait
-  static_assert(VMC == 0 || VMC == 6 || VMC == 8 || VMC == 10 || VMC == 12 || VMC == 16, "vmcnt immediates below");
-  static_assert(BLOCKS % NW == 0, "blocks per wave");
-  static_assert(STAGES * STAGE <= kWideSmemElems, "LDS ring");
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  constexpr int HALF = 128 * kWideBK;             // elements of a half tile
+  constexpr int NA = DBL ? 1 : 2, NB = DBL ? 4 : 2;  // half tiles of a stage
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
   const bf16_t *Wg = (t.g < p.n_experts) ? p.W + (long long)t.g * p.w_stride : p.Ws;
-
-  // Wave w fills blocks w, w + NW, ...; lane l fills row RPB b + l / CPR of its
-  // block at slot l % CPR, i.e. it fetches the chunk that the swizzle puts
-  // there.  Rows past the group's end re-read its first row (in bounds, never
-  // stored).
-  const bf16_t *src[PW];
+  // Wave w fills 1 KiB blocks w and w + 8 of a half tile: rows 8 w .. + 7 and 64
+  // further, lane l the chunk that the swizzle puts at slot l % 8 of row l / 8.
+  const bf16_t *sa[NA][2], *sb[NB][2];
 #pragma unroll
-  for (int i = 0; i < PW; ++i) {
-    const int blk = i * NW + wave;
-    const int r = blk * RPB + lane / CPR;  // stage row: A rows 0..255, then B rows
-    if (r < BM) {
-      const int q = wide_slot<BK>(r, lane % CPR);
-      const int rr = row0 + (r < valid ? r : 0);
+  for (int u = 0; u < 2; ++u) {
+    const int rh = (u * 8 + wave) * 8 + (lane >> 3);  // row of the half tile
+    const int q = wide_slot(rh, lane & 7);
+#pragma unroll
+    for (int h = 0; h < NA; ++h) {
+      const int r = h * 128 + rh;
+      const int rr = row0 + (r < valid ? r : 0);  // padding rows re-read the first one, never stored
       const long long arow = GATE_UP ? (long long)p.row_token[rr] : (long long)rr;
-      src[i] = p.A + arow * p.lda + (long long)t.ks * p.kc + q * 8;
-    } else {
-      const int rb = r - BM;
-      const int q = wide_slot<BK>(rb, lane % CPR);
-      int wrow;
-      if (GATE_UP)
-        wrow = (rb < BN / 2) ? t.nt * (kWideBN / 2) + rb : p.inter + t.nt * (kWideBN / 2) + (rb - BN / 2);
-      else
-        wrow = t.nt * kWideBN + rb;
-      src[i] = Wg + (long long)wrow * p.ldw + (long long)t.ks * p.kc + q * 8;
+      sa[h][u] = p.A + arow * p.lda + (long long)k0 * kWideBK + q * 8;
+    }
+#pragma unroll
+    for (int g = 0; g < NB; ++g) {
+      const int wrow = GATE_UP ? (g & 1) * p.inter + (t.nt + (g >> 1)) * 128 + rh : t.nt * kWideBN + g * 128 + rh;
+      sb[g][u] = Wg + (long long)wrow * p.ldw + (long long)k0 * kWideBK + q * 8;
     }
   }
-  const uint32_t lds0 = lds_addr(smem);
-
+  const uint32_t lds0 = lds_addr(smem) + wave * 1024;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < kWideTM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < kWideTN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  int a_row[TM], b_row[TN];
+  // fragment of k16 step s: row lane % 32 of a 32-row block, chunk 2 s + lane / 32
+  const bf16_t *fa_at[4], *fb_at[4];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) a_row[i] = wm * 128 + i * 32 + (lane & 31);
-#pragma unroll
-  for (int j = 0; j < TN; ++j)
-    b_row[j] = (GATE_UP ? (j < TN / 2 ? 0 : BN / 2) + (j % (TN / 2)) * 32 + wn * 16 * TN : wn * 32 * TN + j * 32) +
-               (lane & 31);
-
-  // Stage kt (clamped to the last of the range: loads past it refill a buffer
-  // that is never read again) into ring buffer BUF.
-#define EXF_W_ISSUE(BUF, KT_)                                                                  \
-  do {                                                                                         \
-    const int k0_ = min((KT_), k1 - 1) * BK;                                                   \
-    const uint32_t base_ = lds0 + (uint32_t)(BUF) * (STAGE * 2);                               \
-    _Pragma("unroll") for (int i_ = 0; i_ < PW; ++i_)                                          \
-        lds_dma16(src[i_] + k0_, base_ + (i_ * NW + wave) * 1024);                             \
-  } while (0)
-#define EXF_W_FRAGS(A_, B_, BUF, S_)                                                           \
-  do {                                                                                         \
-    const bf16_t *As_ = smem + (BUF) * STAGE;                                                  \
-    const bf16_t *Bs_ = As_ + BM * BK;                                                         \
-    const int ch_ = (S_) * 2 + (lane >> 5);                                                    \
-    _Pragma("unroll") for (int i_ = 0; i_ < TMV; ++i_) A_[i_] = *reinterpret_cast<const bf16x8 *>( \
-        As_ + a_row[i_] * BK + wide_slot<BK>(a_row[i_], ch_) * 8);                             \
-    if (TMV > 0)                                                                               \
-      _Pragma("unroll") for (int j_ = 0; j_ < TN; ++j_) B_[j_] = *reinterpret_cast<const bf16x8 *>( \
-          Bs_ + b_row[j_] * BK + wide_slot<BK>(b_row[j_], ch_) * 8);                           \
-  } while (0)
-#define EXF_W_MMA(A_, B_)                                                                      \
-  do {                                                                                         \
-    _Pragma("unroll") for (int i_ = 0; i_ < TMV; ++i_)                                         \
-        _Pragma("unroll") for (int j_ = 0; j_ < TN; ++j_) acc[i_][j_] =                        \
-            __builtin_amdgcn_mfma_f32_32x32x16_bf16(B_[j_], A_[i_], acc[i_][j_], 0, 0, 0);     \
-  } while (0)
-
-  for (int q = 0; q < AHEAD; ++q) EXF_W_ISSUE(q, k0 + q);
-  static_assert((BK / 16) % 2 == 0, "the last step of a stage uses fragment set 1");
-  bf16x8 fa[2][TM], fb[2][TN];
-  int buf = 0;  // ring buffer of stage kt (wave-uniform)
-  for (int kt = k0; kt < k1; ++kt) {
-    // Wait until this wave's loads of stage kt have landed (the later stages
-    // stay in flight) and its LDS reads of the previous stage are done; after
-    // the barrier every wave's part of stage kt is in LDS and nobody reads the
-    // previous buffer any more, so it is refilled with stage kt + AHEAD; then
-    // the k16 steps of stage kt, software-pipelined: the fragments of step s
-    // are read while the MFMAs of step s - 1 run (the last step of a stage,
-    // already in registers, runs after the next barrier).
-    if (VMC == 0)
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (VMC == 6)
-      asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (VMC == 8)
-      asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (VMC == 10)
-      asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (VMC == 12)
-      asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const int prev = (buf == 0) ? STAGES - 1 : buf - 1;
-    EXF_W_ISSUE(prev, kt + AHEAD);
-    {
-#pragma unroll
-      for (int s_ = 0; s_ < BK / 16; ++s_) {
-        EXF_W_FRAGS(fa[s_ & 1], fb[s_ & 1], buf, s_);
-        if (s_ > 0) {
-          EXF_W_MMA(fa[(s_ - 1) & 1], fb[(s_ - 1) & 1]);
-          // one LDS read after each of the first MFMAs
-          constexpr int MF = TMV * TN, RD = TMV > 0 ? TMV + TN : 0, PAIRS = MF < RD ? MF : RD;
-#pragma unroll
-          for (int g_ = 0; g_ < PAIRS; ++g_) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
-          if (MF > PAIRS) __builtin_amdgcn_sched_group_barrier(0x008, MF - PAIRS, 0);
-          if (RD > PAIRS) __builtin_amdgcn_sched_group_barrier(0x100, RD - PAIRS, 0);
-        } else if (kt > k0) {
-          EXF_W_MMA(fa[1], fb[1]);
-        }
-      }
-    }
-    buf = (buf == STAGES - 1) ? 0 : buf + 1;
+  for (int s_ = 0; s_ < 4; ++s_) {
+    const int off = (lane & 31) * kWideBK + wide_slot(lane & 31, 2 * s_ + (lane >> 5)) * 8;
+    fa_at[s_] = smem + wm * 32 * kWideBK + off;
+    fb_at[s_] = smem + 2 * NA * HALF + wn * 32 * kWideBK + off;
   }
-  EXF_W_MMA(fa[1], fb[1]);
-  // the clamped loads past the end land before the ring is refilled or released,
-  // and no wave still reads it
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-#undef EXF_W_ISSUE
-#undef EXF_W_FRAGS
-#undef EXF_W_MMA
+  bf16x8 fa[2][4], fb[2][4];
+
+  // half tiles in LDS: A half h of ring buffer b at slot 2 h + b, B half g at 2 NA + 2 g + b
+#define EXF_P_ISSUE(SRC_, SLOT_)                                                        \
+  do {                                                                                  \
+    _Pragma("unroll") for (int u_ = 0; u_ < 2; ++u_) {                                  \
+      lds_dma16(SRC_[u_], lds0 + (uint32_t)(SLOT_) * (HALF * 2) + u_ * 8192);           \
+      SRC_[u_] += kWideBK;                                                              \
+    }                                                                                   \
+  } while (0)
+#define EXF_P_ISSUE_A(H_, BUF_) EXF_P_ISSUE(sa[H_], 2 * (H_) + (BUF_))
+#define EXF_P_ISSUE_B(G_, BUF_) EXF_P_ISSUE(sb[G_], 2 * NA + 2 * (G_) + (BUF_))
+  // blocks of quadrant row half H_ (tail tiles: always the first)
+#define EXF_P_LIVE(H_, I_) (2 * (DBL ? 0 : (H_)) + (I_) < TMV)
+#define EXF_P_READ_A(H_, BUF_)                                                          \
+  do {                                                                                  \
+    _Pragma("unroll") for (int s_ = 0; s_ < 4; ++s_)                                    \
+        _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_) if (EXF_P_LIVE(H_, i_))        \
+            fa[i_][s_] = *reinterpret_cast<const bf16x8 *>(                             \
+                fa_at[s_] + (2 * (H_) + (BUF_)) * HALF + i_ * 64 * kWideBK);            \
+  } while (0)
+#define EXF_P_READ_B(G_, BUF_)                                                          \
+  do {                                                                                  \
+    if (TMV > 0)                                                                        \
+      _Pragma("unroll") for (int s_ = 0; s_ < 4; ++s_) fb[(G_) & 1][s_] =               \
+          *reinterpret_cast<const bf16x8 *>(fb_at[s_] + (2 * (G_) + (BUF_)) * HALF);    \
+  } while (0)
+#define EXF_P_BARRIER() asm volatile("s_barrier" ::: "memory")
+  // products of row half H_ (full tiles) or weight pair H_ (tail tiles) with weight half J_ of it
+#define EXF_P_MMA(H_, J_)                                                               \
+  do {                                                                                  \
+    __builtin_amdgcn_sched_barrier(0);                                                  \
+    __builtin_amdgcn_s_setprio(1);                                                      \
+    _Pragma("unroll") for (int s_ = 0; s_ < 4; ++s_)                                    \
+        _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_) if (EXF_P_LIVE(H_, i_))        \
+            acc[2 * (H_) + i_][J_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(           \
+                fb[J_][s_], fa[i_][s_], acc[2 * (H_) + i_][J_], 0, 0, 0);               \
+    __builtin_amdgcn_s_setprio(0);                                                      \
+    __builtin_amdgcn_sched_barrier(0);                                                  \
+    EXF_P_BARRIER();                                                                    \
+  } while (0)
+  // at most VM_ of the wave's loads are in flight, then the barrier
+#define EXF_P_WAIT(VM_) asm volatile("s_waitcnt vmcnt(" #VM_ ")\n\ts_barrier" ::: "memory")
+  // One stage of a full tile from ring buffer BUF_.  FILL1_: the first phase issues
+  // the last half tile of the next stage; FILL_: the others issue three of the
+  // stage after it; V1_ .. V4_: loads in flight allowed; NEXT_: a stage follows.
+#define EXF_P_STAGE(BUF_, FILL1_, FILL_, V1_, V2_, V3_, V4_, NEXT_)                     \
+  do {                                                                                  \
+    EXF_P_READ_A(0, BUF_);                                                              \
+    if (FILL1_) EXF_P_ISSUE_A(1, 1 - (BUF_));                                           \
+    EXF_P_WAIT(V1_);                                                                    \
+    EXF_P_MMA(0, BUF_);                                                                 \
+    EXF_P_READ_B(1 - (BUF_), BUF_);                                                     \
+    if (FILL_) EXF_P_ISSUE_B(BUF_, BUF_);                                               \
+    EXF_P_WAIT(V2_);                                                                    \
+    EXF_P_MMA(0, 1 - (BUF_));                                                           \
+    EXF_P_READ_A(1, BUF_);                                                              \
+    if (FILL_) EXF_P_ISSUE_A(0, BUF_);                                                  \
+    EXF_P_WAIT(V3_);                                                                    \
+    EXF_P_MMA(1, 1 - (BUF_));                                                           \
+    if (NEXT_) EXF_P_READ_B(1 - (BUF_), 1 - (BUF_));                                    \
+    if (FILL_) EXF_P_ISSUE_B(1 - (BUF_), BUF_);                                         \
+    EXF_P_WAIT(V4_);                                                                    \
+    EXF_P_MMA(1, BUF_);                                                                 \
+  } while (0)
+  // One stage of a tail tile: FILL1_: B2, B3 of the next stage; FILL_: B0, A, B1 of
+  // the stage after it.
+#define EXF_P_TAIL(BUF_, FILL1_, FILL_, V1_, V2_, V3_, V4_, NEXT_)                      \
+  do {                                                                                  \
+    EXF_P_READ_A(0, BUF_);                                                              \
+    if (FILL1_) EXF_P_ISSUE_B(NB - 2, 1 - (BUF_));                                      \
+    EXF_P_WAIT(V1_);                                                                    \
+    EXF_P_MMA(0, 0);                                                                    \
+    EXF_P_READ_B(1, BUF_);                                                              \
+    if (FILL1_) EXF_P_ISSUE_B(NB - 1, 1 - (BUF_));                                      \
+    if (FILL_) EXF_P_ISSUE_B(0, BUF_);                                                  \
+    EXF_P_WAIT(V2_);                                                                    \
+    EXF_P_MMA(0, 1);                                                                    \
+    EXF_P_READ_B(NB - 2, BUF_);                                                         \
+    if (FILL_) EXF_P_ISSUE_A(0, BUF_);                                                  \
+    EXF_P_WAIT(V3_);                                                                    \
+    EXF_P_MMA(1, 0);                                                                    \
+    EXF_P_READ_B(NB - 1, BUF_);                                                         \
+    if (NEXT_) EXF_P_READ_B(0, 1 - (BUF_));                                             \
+    if (FILL_) EXF_P_ISSUE_B(1, BUF_);                                                  \
+    EXF_P_WAIT(V4_);                                                                    \
+    EXF_P_MMA(1, 1);                                                                    \
+  } while (0)
+  // the loads of the two first stages, in reading order, that no phase issues;
+  // then the first weight half (tiles 0 and 1 have landed)
+#define EXF_P_BEGIN(BUF_)                                                               \
+  do {                                                                                  \
+    EXF_P_ISSUE_B(DBL ? 0 : (BUF_), BUF_);                                              \
+    EXF_P_ISSUE_A(0, BUF_);                                                             \
+    EXF_P_ISSUE_B(DBL ? 1 : 1 - (BUF_), BUF_);                                          \
+    if (DBL) {                                                                          \
+      EXF_P_ISSUE_B(NB - 2, BUF_);                                                      \
+      EXF_P_ISSUE_B(NB - 1, BUF_);                                                      \
+      EXF_P_ISSUE_B(0, 1 - (BUF_));                                                     \
+      EXF_P_ISSUE_A(0, 1 - (BUF_));                                                     \
+      EXF_P_ISSUE_B(1, 1 - (BUF_));                                                     \
+      EXF_P_WAIT(12);                                                                   \
+    } else {                                                                            \
+      EXF_P_ISSUE_A(NA - 1, BUF_);                                                      \
+      EXF_P_ISSUE_B(1 - (BUF_), 1 - (BUF_));                                            \
+      EXF_P_ISSUE_A(0, 1 - (BUF_));                                                     \
+      EXF_P_ISSUE_B(BUF_, 1 - (BUF_));                                                  \
+      EXF_P_WAIT(10);                                                                   \
+    }                                                                                   \
+    EXF_P_READ_B(DBL ? 0 : (BUF_), BUF_);                                               \
+  } while (0)
+
+  // an odd count of stages starts in buffer 1, so the last stage is always in buffer 1
+  int left = k1 - k0 - 2;
+  const bool odd = left & 1;
+  if (odd)
+    EXF_P_BEGIN(1);
+  else
+    EXF_P_BEGIN(0);
+  if (wave >= 4) EXF_P_BARRIER();  // half a phase behind
+  if constexpr (DBL) {
+    if (odd) {
+      EXF_P_TAIL(1, true, true, 12, 14, 12, 12, true);
+      --left;
+    }
+    for (; left > 0; left -= 2) {
+      EXF_P_TAIL(0, true, true, 12, 14, 12, 12, true);
+      EXF_P_TAIL(1, true, true, 12, 14, 12, 12, true);
+    }
+    EXF_P_TAIL(0, true, false, 12, 12, 8, 6, true);
+    EXF_P_TAIL(1, false, false, 4, 2, 0, 0, false);
+  } else {
+    if (odd) {
+      EXF_P_STAGE(1, true, true, 10, 10, 10, 10, true);
+      --left;
+    }
+    for (; left > 0; left -= 2) {
+      EXF_P_STAGE(0, true, true, 10, 10, 10, 10, true);
+      EXF_P_STAGE(1, true, true, 10, 10, 10, 10, true);
+    }
+    EXF_P_STAGE(0, true, false, 10, 8, 6, 4, true);
+    EXF_P_STAGE(1, false, false, 2, 0, 0, 0, false);
+  }
+  if (wave < 4) EXF_P_BARRIER();
+#undef EXF_P_ISSUE
+#undef EXF_P_ISSUE_A
+#undef EXF_P_ISSUE_B
+#undef EXF_P_LIVE
+#undef EXF_P_READ_A
+#undef EXF_P_READ_B
+#undef EXF_P_BARRIER
+#undef EXF_P_MMA
+#undef EXF_P_WAIT
+#undef EXF_P_STAGE
+#undef EXF_P_TAIL
+#undef EXF_P_BEGIN
+}
+
+// Tile row and column of accumulator tile (i, j) of wave (wm, wn), and the
+// output column of gate/up pair (i, 0), (i, 1).
+template <bool DBL> __device__ __forceinline__ int wide_row(int wm, int i) {
+  return (DBL ? 0 : (i >> 1) * 128) + (i & 1) * 64 + wm * 32;
+}
+template <bool DBL> __device__ __forceinline__ int wide_col(int wn, int i, int j) {
+  return (DBL ? (i >> 1) * kWideBN : 0) + j * 128 + wn * 32;
+}
+template <bool DBL> __device__ __forceinline__ int wide_pair_col(int wn, int i) {
+  return (DBL ? (i >> 1) * 128 : 0) + wn * 32;
 }
 
 // Accumulator layout: the MFMAs take the weight fragment as their first
 // operand, so register r of tile (i, j) of wave (wm, wn) holds tile row (token)
-// 128 wm + 32 i + lane % 32 and tile column 32 TN wn + 32 j + 8 (r / 4) +
-// 4 (lane / 32) + r % 4: each lane owns four runs of four consecutive columns of
-// one row, stored 8 (bf16) or 16 (fp32) bytes at a time.
+// wide_row + lane % 32 and tile column wide_col + 8 (r / 4) + 4 (lane / 32) +
+// r % 4: each lane owns four runs of four consecutive columns of one row,
+// stored 8 (bf16) or 16 (fp32) bytes at a time.
 __device__ __forceinline__ void store4_bf16(bf16_t *dst, float a, float b, float c, float d) {
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
   const bf16x4 v = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};   // two v_cvt_pk_bf16_f32
@@ -597,38 +682,34 @@ __device__ __forceinline__ void store4_bf16_nt(bf16_t *dst, float a, float b, fl
 // Finished tile: gate/up writes H = SiLU(gate) * up; down writes y (direct)
 // or fp32 rows Y scaled by the row's routing weight, or unscaled bf16 rows Yh
 // (the combine applies the weight).
-template <bool GATE_UP, bool DIRECT, int NW, bool DBL>
+template <bool GATE_UP, bool DIRECT, bool DBL>
 __device__ __forceinline__ void wide_store(const GemmKArgs &p, const TileId &t, int row0, int valid,
                                            const f32x16 (&acc)[kWideTM][kWideTN]) {
-  constexpr int WN = DBL ? NW : NW / 2, TN = kWideTN;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave >> 2, wn = wave & 3;
   const int c4 = 4 * (lane >> 5);
 #pragma unroll
   for (int i = 0; i < kWideTM; ++i) {
-    const int ml = wm * 128 + i * 32 + (lane & 31);
+    const int ml = wide_row<DBL>(wm, i) + (lane & 31);
     if (ml >= valid) continue;
     const int row = row0 + ml;
     if (GATE_UP) {
-      bf16_t *dst = p.H + (long long)row * p.inter + t.nt * (kWideBN / 2) + wn * 16 * TN + c4;
+      bf16_t *dst = p.H + (long long)row * p.inter + t.nt * (kWideBN / 2) + wide_pair_col<DBL>(wn, i) + c4;
+      const f32x16 &gt = acc[i][0], &up = acc[i][1];
 #pragma unroll
-      for (int j = 0; j < TN / 2; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x16 &gt = acc[i][j], &up = acc[i][j + TN / 2];
-          store4_bf16(dst + j * 32 + 8 * g, silu(gt[4 * g]) * up[4 * g], silu(gt[4 * g + 1]) * up[4 * g + 1],
-                      silu(gt[4 * g + 2]) * up[4 * g + 2], silu(gt[4 * g + 3]) * up[4 * g + 3]);
-        }
+      for (int g = 0; g < 4; ++g)
+        store4_bf16(dst + 8 * g, silu(gt[4 * g]) * up[4 * g], silu(gt[4 * g + 1]) * up[4 * g + 1],
+                    silu(gt[4 * g + 2]) * up[4 * g + 2], silu(gt[4 * g + 3]) * up[4 * g + 3]);
     } else {
       const float w = p.Yh && !DIRECT ? 1.f : p.row_w[row];
-      const int n0 = t.nt * kWideBN + wn * 32 * TN + c4;
+      const int n0 = t.nt * kWideBN + c4;
       const long long base = DIRECT ? (long long)p.row_token[row] * p.d : (long long)row * p.d;
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < kWideTN; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x16 &c = acc[i][j];
-          const int n = n0 + j * 32 + 8 * g;
+          const int n = n0 + wide_col<DBL>(wn, i, j) + 8 * g;
           const float v0 = c[4 * g] * w, v1 = c[4 * g + 1] * w, v2 = c[4 * g + 2] * w, v3 = c[4 * g + 3] * w;
           if (DIRECT)
             store4_bf16_nt(p.y + base + n, v0, v1, v2, v3);
@@ -654,37 +735,34 @@ __device__ __forceinline__ void wide_store(const GemmKArgs &p, const TileId &t, 
 template <bool GATE_UP, bool DIRECT, int NW, bool DBL>
 __device__ __forceinline__ void wide_store_lds(const GemmKArgs &p, const TileId &t, int row0, int valid,
                                                const f32x16 (&acc)[kWideTM][kWideTN], bf16_t *smem) {
-  constexpr int WN = DBL ? NW : NW / 2, TN = kWideTN, BM = DBL ? kWide / 2 : kWide;
-  constexpr int COLS = (GATE_UP ? 16 : 32) * TN * WN;        // output columns of the tile
+  constexpr int BM = DBL ? kWide / 2 : kWide;
+  constexpr int COLS = (DBL ? 2 : 1) * kWideBN / (GATE_UP ? 2 : 1);  // output columns of the tile
   constexpr int PITCH = COLS * 2 + 16;                        // LDS bytes per row (padded)
   static_assert(BM * PITCH <= kWideSmemElems * 2, "staging tile fits the ring");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave >> 2, wn = wave & 3;
   const int c4 = 4 * (lane >> 5);
   char *lds = reinterpret_cast<char *>(smem);
 #pragma unroll
   for (int i = 0; i < kWideTM; ++i) {
-    const int ml = wm * 128 + i * 32 + (lane & 31);
+    const int ml = wide_row<DBL>(wm, i) + (lane & 31);
     const float w = (!GATE_UP && DIRECT && ml < valid) ? p.row_w[row0 + ml] : 1.f;
-    char *rowp = lds + ml * PITCH;
+    bf16_t *rowp = reinterpret_cast<bf16_t *>(lds + ml * PITCH) + c4;
     if (GATE_UP) {
+      const f32x16 &gt = acc[i][0], &up = acc[i][1];
 #pragma unroll
-      for (int j = 0; j < TN / 2; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x16 &gt = acc[i][j], &up = acc[i][j + TN / 2];
-          store4_bf16(reinterpret_cast<bf16_t *>(rowp) + wn * 16 * TN + j * 32 + 8 * g + c4,
-                      silu(gt[4 * g]) * up[4 * g], silu(gt[4 * g + 1]) * up[4 * g + 1],
-                      silu(gt[4 * g + 2]) * up[4 * g + 2], silu(gt[4 * g + 3]) * up[4 * g + 3]);
-        }
+      for (int g = 0; g < 4; ++g)
+        store4_bf16(rowp + wide_pair_col<DBL>(wn, i) + 8 * g, silu(gt[4 * g]) * up[4 * g],
+                    silu(gt[4 * g + 1]) * up[4 * g + 1], silu(gt[4 * g + 2]) * up[4 * g + 2],
+                    silu(gt[4 * g + 3]) * up[4 * g + 3]);
     } else {
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < kWideTN; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x16 &c = acc[i][j];
-          store4_bf16(reinterpret_cast<bf16_t *>(rowp) + wn * 32 * TN + j * 32 + 8 * g + c4, c[4 * g] * w,
-                      c[4 * g + 1] * w, c[4 * g + 2] * w, c[4 * g + 3] * w);
+          store4_bf16(rowp + wide_col<DBL>(wn, i, j) + 8 * g, c[4 * g] * w, c[4 * g + 1] * w, c[4 * g + 2] * w,
+                      c[4 * g + 3] * w);
         }
     }
   }
@@ -742,18 +820,18 @@ __device__ __forceinline__ WideSplit wide_split(const GemmKArgs &p, int G) {
 // Partial tile in the accumulator layout: row-major, 256 (DBL: 512) columns.
 template <bool DBL>
 __device__ __forceinline__ void wide_store_partial(float *P, const f32x16 (&acc)[kWideTM][kWideTN]) {
-  constexpr int WN = DBL ? kWideWaves : kWideWaves / 2, BN = 32 * kWideTN * WN;
+  constexpr int BN = DBL ? 2 * kWideBN : kWideBN;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave >> 2, wn = wave & 3;
 #pragma unroll
   for (int i = 0; i < kWideTM; ++i) {
-    float *prow = P + (wm * 128 + i * 32 + (lane & 31)) * BN + wn * 32 * kWideTN + 4 * (lane >> 5);
+    float *prow = P + (wide_row<DBL>(wm, i) + (lane & 31)) * BN + 4 * (lane >> 5);
 #pragma unroll
     for (int j = 0; j < kWideTN; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const f32x16 &c = acc[i][j];
-        *reinterpret_cast<float4 *>(prow + j * 32 + 8 * g) =
+        *reinterpret_cast<float4 *>(prow + wide_col<DBL>(wn, i, j) + 8 * g) =
             make_float4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
       }
   }
@@ -784,39 +862,37 @@ __device__ __forceinline__ void wide_gemm(const GemmKArgs &p, int G, bf16_t *sme
   f32x16 acc[kWideTM][kWideTN];
   // the wave's 32-row blocks that hold rows of the group (wave-uniform)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  auto blocks = [&](int valid, int wm) { return max(0, min(kWideTM, (valid - wm * 128 + 31) >> 5)); };
-#define EXF_W_MAIN(DBL_, TMV_) \
-  wide_tile_mma<GATE_UP, kWideBK, kWideStages, NW, DBL_, TMV_>(p, t, row0, valid, k0, k1, smem, acc)
-#define EXF_W_DISPATCH(DBL_, TMV_VAL)                                                          \
-  switch (TMV_VAL) {                                                                           \
-    case 4: EXF_W_MAIN(DBL_, 4); break;                                                        \
-    case 3: EXF_W_MAIN(DBL_, 3); break;                                                        \
-    case 2: EXF_W_MAIN(DBL_, 2); break;                                                        \
-    case 1: EXF_W_MAIN(DBL_, 1); break;                                                        \
-    default: EXF_W_MAIN(DBL_, 0); break;                                                       \
-  }
-  static_assert(kWideTM == 4, "the dispatch below covers 0 .. 4 valid row blocks");
+#define EXF_W_MAIN(DBL_, TMV_) wide_tile_mma<GATE_UP, DBL_, TMV_>(p, t, row0, valid, k0, k1, smem, acc)
+  // the 32-row blocks 64 i + 32 wm of 128 rows, `rows` of which hold rows of the group
+  auto live = [&](int rows) { return max(0, min(2, (rows - 32 * (wave >> 2) + 63) >> 6)); };
   if (__builtin_amdgcn_readfirstlane(t.dbl)) {
     const int valid = min(kWide / 2, p.offsets[t.g + 1] - row0);
-    EXF_W_DISPATCH(true, blocks(valid, 0))
+    switch (live(valid)) {
+      case 2: EXF_W_MAIN(true, 2); break;
+      case 1: EXF_W_MAIN(true, 1); break;
+      default: EXF_W_MAIN(true, 0); break;
+    }
     if (part)
       wide_store_partial<true>(part, acc);
     else if (!GATE_UP && !DIRECT && p.Yh)
       wide_store_lds<GATE_UP, DIRECT, NW, true>(p, t, row0, valid, acc, smem);
     else
-      wide_store<GATE_UP, DIRECT, NW, true>(p, t, row0, valid, acc);
+      wide_store<GATE_UP, DIRECT, true>(p, t, row0, valid, acc);
   } else {
-    const int valid = min(kWide, p.offsets[t.g + 1] - row0);
-    EXF_W_DISPATCH(false, blocks(valid, wave / (NW / 2)))
+    const int valid = min(kWide, p.offsets[t.g + 1] - row0);  // more than 128
+    switch (2 + live(valid - 128)) {
+      case 4: EXF_W_MAIN(false, 4); break;
+      case 3: EXF_W_MAIN(false, 3); break;
+      default: EXF_W_MAIN(false, 2); break;
+    }
     if (part)
       wide_store_partial<false>(part, acc);
     else if (!GATE_UP && !DIRECT && p.Yh)
       wide_store_lds<GATE_UP, DIRECT, NW, false>(p, t, row0, valid, acc, smem);
     else
-      wide_store<GATE_UP, DIRECT, NW, false>(p, t, row0, valid, acc);
+      wide_store<GATE_UP, DIRECT, false>(p, t, row0, valid, acc);
   }
 #undef EXF_W_MAIN
-#undef EXF_W_DISPATCH
 }
 
 
@@ -870,9 +946,9 @@ __global__ __launch_bounds__(256) void expert_wide_fixup(const GemmKArgs p, int 
   if (GATE_UP) {
     for (int q = 0; q < bn / 128; ++q) {
       const int col = q * 64 + (threadIdx.x & 15) * 4;
-      // gate tile (col / 32) % (TN / 2) of wave col / (16 TN); its up tile TN / 2 further
-      const int pc = (col / (16 * kWideTN)) * 32 * kWideTN + ((col >> 5) % (kWideTN / 2)) * 32 + (col & 31);
-      const float4 g = sum4(pc), u = sum4(pc + 16 * kWideTN);
+      // H column col of the tile: gate column col % 128 of n-tile col / 128, up 128 further
+      const int pc = (col >> 7) * kWideBN + (col & 127);
+      const float4 g = sum4(pc), u = sum4(pc + 128);
       const float h[4] = {silu(g.x) * u.x, silu(g.y) * u.y, silu(g.z) * u.z, silu(g.w) * u.w};
       bf16_t *dst = p.H + (long long)row * p.inter + t.nt * (kWideBN / 2) + col;
 #pragma unroll

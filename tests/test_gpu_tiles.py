@@ -1,6 +1,8 @@
 """Kernel edges against the oracle: tile remainders, the smallest and the largest of a
 kernel's range, and either side of a dispatch rule."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -98,3 +100,22 @@ def test_float32_router_logits(n, T, d):
     assert np.all(np.abs(got.astype(np.float64) - ref) <= logits_bound(xs, lp.ref.w_router, lp.ref.router_bias, d))
     r_ids, _ = O.route(got, 2)
     np.testing.assert_array_equal(dbg["topk_ids"].cpu().numpy(), r_ids)
+
+
+# Wide tiles: full tiles (129 to 256 rows of the last 256) and 128 x 512 tails (1 to 128 rows)
+# either side of every 32-row block, reductions of two stages (d 128, gate/up only), eight (d 512)
+# and split ones of even and odd lengths (I 2048 and 2816 in the last, partial round of the down
+# projection), outputs straight to y (one route a token) and as bf16 rows.
+@pytest.mark.parametrize("d,inter,k", [(128, 2048, 1), (512, 2048, 1), (512, 2816, 2), (1024, 1536, 2)])
+def test_wide_tile_edges(d, inter, k):
+    sizes = [129, 160, 161, 192, 193, 224, 225, 256, 257, 288, 289, 320, 321, 352, 353, 384, 1, 32, 33, 64, 65, 96,
+             97, 128, 0, 700]
+    sizes[-1] += sum(sizes) % k
+    ids = np.random.default_rng(d).permutation(np.repeat(np.arange(len(sizes)), sizes)).astype(np.int32)
+    ids = ids.reshape(-1, k)
+    shape = _shape(d, inter, len(sizes), k, dtype="bf16")
+    plan = (ctypes.c_int32 * 10)()
+    lp = X._Layer(d, inter, len(sizes), k, 0, X.BF16, 0, 0x10000, None, 0x10000, 0x10000, None, None)
+    assert X.lib().exfold_gemm_plan(ctypes.byref(lp), ids.size, len(sizes), 256, plan) == X.OK
+    assert plan[0] == 3 and plan[5] == (3 if d % 512 == 0 else 1)
+    assert _execute(shape, ids.shape[0], ids, seed=4) <= TOL_Y["bf16"]
