@@ -334,8 +334,9 @@ const char *exfold_status_str(exfold_status status);
 /* Kernel families of the expert GEMMs (exfold_gemm_plan). */
 enum {
   EXFOLD_GEMM_SIMT = 0,    /* float32 layers                                          */
-  EXFOLD_GEMM_TILE = 1,    /* 128x128 MFMA tiles                                      */
-  EXFOLD_GEMM_SKINNY = 2,  /* 32x64 tiles streaming weights (few rows per expert)     */
+  EXFOLD_GEMM_TILE = 1,    /* MFMA tiles of 128 columns, 64 or 128 rows               */
+  EXFOLD_GEMM_SKINNY = 2,  /* 32x64 and 64x64 tiles streaming weights (few rows per
+                              expert)                                                 */
   EXFOLD_GEMM_WIDE = 3     /* 256x256 tiles (128x512 tails) in rounds of one per CU   */
 };
 

@@ -48,6 +48,21 @@ __device__ __forceinline__ float silu(float g) { return g * __builtin_amdgcn_rcp
 
 constexpr int kBK = 64;
 
+// 16 bytes of a weight row; ONCE: no other tile reads it (TileId::alone), and the
+// load is non-temporal.  Such streams neither evict the rows, tables and
+// activations that are read again nor wait for the room: Mixtral-shaped
+// decode gate/up 163 -> 149 us, down 85 -> 77, GLM-shaped (64 tokens, pool of 32)
+// 141 -> 129 and 79 -> 71.  Where several m-tiles share a weight row the hint costs
+// more than it gives (64-row down tiles of 512 Qwen3-shaped tokens, pool of 64,
+// 55 -> 68; every wide tile 5%).
+template <bool ONCE>
+__device__ __forceinline__ u32x4 load_w16(const bf16_t *p) {
+  if constexpr (ONCE)
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+  else
+    return *reinterpret_cast<const u32x4 *>(p);
+}
+
 // LDS element offset of 16-byte chunk q of tile row r (8 chunks per 128-byte row).
 // The slot is q XOR gray(r): one chunk column of any 8 or 16 consecutive rows
 // (the lanes of one LDS cycle of ds_read_b128) then spans distinct banks.
@@ -61,6 +76,7 @@ __device__ __forceinline__ int swz(int r, int q) { return (r * 8 + (q ^ ((r ^ (r
 struct TileId {
   int g, nt, ks, mt;
   int dbl;  // wide tiles: a 128-row tail spanning n-tiles nt and nt + 1
+  int alone;  // the group has one m-tile: nobody else reads this tile's weights
 };
 // Tile of logical id L (m-tile fastest within a group and n-tile).
 __device__ __forceinline__ void tile_at(const GemmKArgs &p, int L, TileId &t) {
@@ -74,6 +90,7 @@ __device__ __forceinline__ void tile_at(const GemmKArgs &p, int L, TileId &t) {
   const int local = L - p.tile_start[lo] * units;
   t.g = lo;
   t.mt = local % mt_g;
+  t.alone = mt_g == 1;
   const int u = local / mt_g;
   t.ks = u % p.ksplit;
   t.nt = u / p.ksplit;
@@ -93,7 +110,7 @@ __device__ __forceinline__ bool decode_tile(const GemmKArgs &p, int wg, TileId &
 // PLAIN: one group of p.rows rows read in order (no offsets, tile list or
 // gather), partial sums of split ks written unscaled to Y[ks] (a plain
 // x W^T with a split reduction: the router logits of large batches).
-template <int BM, int BN, int STAGES, bool GATE_UP, bool DIRECT, bool PLAIN = false>
+template <int BM, int BN, bool GATE_UP, bool DIRECT, bool PLAIN = false>
 __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
   constexpr int WTM = BM / 2, WTN = BN / 2;
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -114,6 +131,7 @@ __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
     const int L = xcd_remap(blockIdx.x, total);
     t.g = 0;
     t.mt = L % mt_n;
+    t.alone = 0;
     t.ks = (L / mt_n) % p.ksplit;
     t.nt = L / mt_n / p.ksplit;
     row0 = t.mt * BM;
@@ -174,8 +192,7 @@ __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
   do {                                                                                       \
     _Pragma("unroll") for (int i_ = 0; i_ < PA; ++i_) if (a_live[i_]) RA[i_] =               \
         *reinterpret_cast<const u32x4 *>(a_src[i_] + (K0));                                  \
-    _Pragma("unroll") for (int i_ = 0; i_ < PB; ++i_) RB[i_] =                               \
-        *reinterpret_cast<const u32x4 *>(b_src[i_] + (K0));                                  \
+    _Pragma("unroll") for (int i_ = 0; i_ < PB; ++i_) RB[i_] = load_w16<ONCE>(b_src[i_] + (K0)); \
   } while (0)
 #define EXF_LSTORE(RA, RB, BUF)                                                              \
   do {                                                                                       \
@@ -238,13 +255,14 @@ __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
 
   // Pairs of phases over the two LDS buffers, no early exit (one loop exit keeps
   // the accumulators in one register set); an odd tile count ends with buffer 0.
-  // Loads past the last tile re-read the last tile (k clamped) and land in a
-  // buffer that is never read again, so each phase is one straight-line block.
+  // LDS buffer (kt & 1) holds tile kt and the other register set holds tile kt + 1,
+  // so each tile's loads are covered by two compute phases.  Loads past the last
+  // tile re-read the last tile (k clamped) and land in a buffer that is never read
+  // again, so each phase is one straight-line block.
   const int KT = p.kc / kBK;
   const int k_last = (KT - 1) * kBK;
-  if (STAGES == 2) {
-    // LDS buffer (kt & 1) holds tile kt; the other register set holds tile kt + 1,
-    // so each tile's loads are covered by two compute phases.
+  auto main_loop = [&](auto once) __attribute__((always_inline)) {
+    constexpr bool ONCE = decltype(once)::value;
     u32x4 ra0[PA], rb0[PB], ra1[PA], rb1[PB];
     _Pragma("unroll") for (int i_ = 0; i_ < PA; ++i_) ra0[i_] = ra1[i_] = u32x4{0u, 0u, 0u, 0u};
     EXF_GLOAD(ra0, rb0, 0);
@@ -265,28 +283,11 @@ __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
       __syncthreads();
     }
     if (kt < KT) EXF_COMPUTE(0);
-  } else {
-    // One tile of loads in flight, covered by one compute phase.
-    u32x4 ra[PA], rb[PB];
-    _Pragma("unroll") for (int i_ = 0; i_ < PA; ++i_) ra[i_] = u32x4{0u, 0u, 0u, 0u};
-    EXF_GLOAD(ra, rb, 0);
-    EXF_LSTORE(ra, rb, 0);
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 2 <= KT; kt += 2) {
-      EXF_GLOAD(ra, rb, (kt + 1) * kBK);
-      EXF_COMPUTE(0);
-      EXF_LSTORE(ra, rb, 1);
-      EXF_SCHEDULE();
-      __syncthreads();
-      EXF_GLOAD(ra, rb, min((kt + 2) * kBK, k_last));
-      EXF_COMPUTE(1);
-      EXF_LSTORE(ra, rb, 0);
-      EXF_SCHEDULE();
-      __syncthreads();
-    }
-    if (kt < KT) EXF_COMPUTE(0);
-  }
+  };
+  if (!PLAIN && __builtin_amdgcn_readfirstlane(t.alone))
+    main_loop(std::true_type{});
+  else
+    main_loop(std::false_type{});
 #undef EXF_GLOAD
 #undef EXF_LSTORE
 #undef EXF_COMPUTE
@@ -975,22 +976,24 @@ __global__ __launch_bounds__(256) void expert_wide_fixup(const GemmKArgs p, int 
 }
 
 // ---------------------------------------------------------------------------
-// Skinny tile for decode (few rows per retained expert): 32 rows x 64 output
+// Skinny tile for decode (few rows per retained expert): 32 RB rows x 64 output
 // columns (gate/up: 32 gate + 32 up columns), BK = 128 per stage (256 contiguous
 // bytes of every weight row per load step), and the four waves split each
 // stage's reduction (wave w takes k16 steps w and w + 4) instead of the tile, so
-// the weights stream through many small workgroups (three per CU by LDS).  The
-// four partial tiles are added in wave order through LDS at the end.
+// the weights stream through many small workgroups (three per CU by LDS for RB
+// = 1, two for RB = 2).  The four partial tiles are added in wave order through
+// LDS at the end.  A weight row that skips LDS (each wave loading its own MFMA
+// fragments, 64-byte pieces of 16 rows) streams 25-35% slower.
 // ---------------------------------------------------------------------------
-constexpr int kSkM = 32, kSkN = 64, kSkK = 128;
+constexpr int kSkN = 64, kSkK = 128;
 
 // LDS element offset of 16-byte chunk q of row r in a 256-byte row (16 chunks):
 // q XOR (r mod 16) spreads one chunk column of 16 consecutive rows over all banks.
 __device__ __forceinline__ int swz16(int r, int q) { return (r * 16 + (q ^ (r & 15))) * 8; }
 
-template <bool GATE_UP, bool DIRECT>
-__global__ __launch_bounds__(256) void expert_gemm_skinny(const GemmKArgs p) {
-  constexpr int PA = kSkM * 16 / 256, PB = kSkN * 16 / 256;  // 16-byte chunks per thread per stage
+template <int RB, bool GATE_UP, bool DIRECT>
+__global__ __launch_bounds__(256, RB == 1 ? 3 : 2) void expert_gemm_skinny(const GemmKArgs p) {
+  constexpr int kSkM = 32 * RB, PA = kSkM * 16 / 256, PB = kSkN * 16 / 256;  // 16-byte chunks per thread per stage
   constexpr int STAGE = (kSkM + kSkN) * kSkK;                  // elements per LDS stage
   __shared__ __attribute__((aligned(16))) bf16_t smem[2 * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1022,18 +1025,22 @@ __global__ __launch_bounds__(256) void expert_gemm_skinny(const GemmKArgs p) {
     b_src[i] = Wg + (long long)wrow * p.ldw + (long long)t.ks * p.kc + (c & 15) * 8;
   }
 
-  f32x16 acc[2];
+  f32x16 acc[RB][2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const bool two = RB == 2 && __builtin_amdgcn_readfirstlane(valid) > 32;  // the second row block holds rows
 
-#define EXF_SK_GLOAD(RA, RB, K0)                                                            \
+  // stage KT_ (past the end: the last one again, into a buffer that is not read)
+#define EXF_SK_GLOAD(RA_, RB_, KT_)                                                         \
   do {                                                                                      \
-    _Pragma("unroll") for (int i_ = 0; i_ < PA; ++i_) RA[i_] =                              \
-        *reinterpret_cast<const u32x4 *>(a_src[i_] + (K0));                                 \
-    _Pragma("unroll") for (int i_ = 0; i_ < PB; ++i_) RB[i_] =                              \
-        *reinterpret_cast<const u32x4 *>(b_src[i_] + (K0));                                 \
+    const int k_ = min((KT_) * kSkK, k_last);                                               \
+    _Pragma("unroll") for (int i_ = 0; i_ < PA; ++i_) RA_[i_] =                             \
+        *reinterpret_cast<const u32x4 *>(a_src[i_] + k_);                                   \
+    _Pragma("unroll") for (int i_ = 0; i_ < PB; ++i_) RB_[i_] = load_w16<true>(b_src[i_] + k_); \
   } while (0)
 #define EXF_SK_LSTORE(RA, RB, BUF)                                                          \
   do {                                                                                      \
@@ -1049,89 +1056,103 @@ __global__ __launch_bounds__(256) void expert_gemm_skinny(const GemmKArgs p) {
     }                                                                                       \
   } while (0)
   // wave w: k16 steps w and w + 4 of the stage; lane l reads row l % 32, 8 k at (l / 32) * 8
-#define EXF_SK_COMPUTE(BUF)                                                                 \
+#define EXF_SK_COMPUTE(BUF, KT_)                                                            \
   do {                                                                                      \
     const bf16_t *As_ = smem + (BUF) * STAGE;                                               \
     const bf16_t *Bs_ = As_ + kSkM * kSkK;                                                  \
     _Pragma("unroll") for (int h_ = 0; h_ < 2; ++h_) {                                      \
+      if (h_ == 0 && half && (KT_) == KT - 1) continue;                                     \
       const int ch_ = (wave + 4 * h_) * 2 + (lane >> 5);                                    \
       const bf16x8 a_ = *reinterpret_cast<const bf16x8 *>(&As_[swz16(lane & 31, ch_)]);     \
       const bf16x8 b0_ = *reinterpret_cast<const bf16x8 *>(&Bs_[swz16(lane & 31, ch_)]);    \
       const bf16x8 b1_ = *reinterpret_cast<const bf16x8 *>(&Bs_[swz16(32 + (lane & 31), ch_)]); \
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b0_, acc[0], 0, 0, 0);           \
-      acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b1_, acc[1], 0, 0, 0);           \
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b0_, acc[0][0], 0, 0, 0);     \
+      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b1_, acc[0][1], 0, 0, 0);     \
+      if (two) {                                                                            \
+        const bf16x8 c_ = *reinterpret_cast<const bf16x8 *>(&As_[swz16(32 + (lane & 31), ch_)]); \
+        acc[RB - 1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c_, b0_, acc[RB - 1][0], 0, 0, 0); \
+        acc[RB - 1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c_, b1_, acc[RB - 1][1], 0, 0, 0); \
+      }                                                                                     \
     }                                                                                       \
   } while (0)
 
   // Two register sets: the loads of stage kt + 2 fly during the MFMAs of stage kt.
-  const int KT = p.kc / kSkK;
-  const int k_last = (KT - 1) * kSkK;
+  // The last stage always ends with the range; when only 64 of its columns are
+  // new, the k16 steps of its lower half are not taken again.
+  const int KT = (p.kc + kSkK - 1) / kSkK, k_last = p.kc - kSkK;
+  const bool half = (p.kc & (kSkK - 1)) != 0;
   u32x4 ra0[PA], rb0[PB], ra1[PA], rb1[PB];
   EXF_SK_GLOAD(ra0, rb0, 0);
   EXF_SK_LSTORE(ra0, rb0, 0);
-  EXF_SK_GLOAD(ra1, rb1, min(kSkK, k_last));
+  EXF_SK_GLOAD(ra1, rb1, 1);
   __syncthreads();
   int kt = 0;
   for (; kt + 2 <= KT; kt += 2) {
-    EXF_SK_GLOAD(ra0, rb0, min((kt + 2) * kSkK, k_last));
-    EXF_SK_COMPUTE(0);
+    EXF_SK_GLOAD(ra0, rb0, kt + 2);
+    EXF_SK_COMPUTE(0, kt);
     EXF_SK_LSTORE(ra1, rb1, 1);
     __syncthreads();
-    EXF_SK_GLOAD(ra1, rb1, min((kt + 3) * kSkK, k_last));
-    EXF_SK_COMPUTE(1);
+    EXF_SK_GLOAD(ra1, rb1, kt + 3);
+    EXF_SK_COMPUTE(1, kt + 1);
     EXF_SK_LSTORE(ra0, rb0, 0);
     __syncthreads();
   }
-  if (kt < KT) EXF_SK_COMPUTE(0);
+  if (kt < KT) EXF_SK_COMPUTE(0, kt);
 #undef EXF_SK_GLOAD
 #undef EXF_SK_LSTORE
 #undef EXF_SK_COMPUTE
 
   // Partial tiles of the four waves, added in wave order (LDS reused).
-  __syncthreads();
   float *red = reinterpret_cast<float *>(smem);  // [4][2][16][64] floats = 32 KB
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < RB; ++i) {
+    if (i > 0 && !two) break;
+    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[((wave * 2 + j) * 16 + r) * 64 + lane] = acc[j][r];
-  __syncthreads();
-  // wave w finishes accumulator registers r in [4 w, 4 w + 4) of both column halves
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+      for (int r = 0; r < 16; ++r) red[((wave * 2 + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+    __syncthreads();
+    // wave w finishes accumulator registers r in [4 w, 4 w + 4) of both column halves:
+    // rows (r / 4) * 8 + (lane / 32) * 4 + r % 4 of the 32x32 MFMA layout
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = wave * 4 + q;
-      float v = red[((0 * 2 + j) * 16 + r) * 64 + lane];
+      float v[2];
 #pragma unroll
-      for (int w = 1; w < 4; ++w) v += red[((w * 2 + j) * 16 + r) * 64 + lane];
-      acc[j][q] = v;
-    }
-
-  // ---- epilogue: rows (r / 4) * 8 + (lane / 32) * 4 + r % 4 of the 32x32 MFMA layout ----
+      for (int j = 0; j < 2; ++j) {
+        v[j] = red[((0 * 2 + j) * 16 + r) * 64 + lane];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = wave * 4 + q;
-    const int ml = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-    if (ml < valid) {
-      const int row = row0 + ml;
-      if (GATE_UP) {
-        const int n = t.nt * (kSkN / 2) + (lane & 31);
-        p.H[(long long)row * p.inter + n] = f32_to_bf16(silu(acc[0][q]) * acc[1][q]);
-      } else {
-        const float w = p.row_w[row];
+        for (int w = 1; w < 4; ++w) v[j] += red[((w * 2 + j) * 16 + r) * 64 + lane];
+      }
+      const int ml = i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+      if (ml < valid) {
+        const int row = row0 + ml;
+        if (GATE_UP) {
+          const int n = t.nt * (kSkN / 2) + (lane & 31);
+          p.H[(long long)row * p.inter + n] = f32_to_bf16(silu(v[0]) * v[1]);
+        } else {
+          const float w = p.row_w[row];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int n = t.nt * kSkN + j * 32 + (lane & 31);
-          if (DIRECT)
-            p.y[(long long)p.row_token[row] * p.d + n] = f32_to_bf16(acc[j][q] * w);
-          else if (p.Yh)
-            p.Yh[(long long)row * p.d + n] = f32_to_bf16(acc[j][q]);
-          else
-            p.Y[((long long)t.ks * p.rows + row) * p.d + n] = acc[j][q] * w;
+          for (int j = 0; j < 2; ++j) {
+            const int n = t.nt * kSkN + j * 32 + (lane & 31);
+            if (DIRECT)
+              p.y[(long long)p.row_token[row] * p.d + n] = f32_to_bf16(v[j] * w);
+            else if (p.Yh)
+              p.Yh[(long long)row * p.d + n] = f32_to_bf16(v[j]);
+            else
+              p.Y[((long long)t.ks * p.rows + row) * p.d + n] = v[j] * w;
+          }
         }
       }
     }
   }
+}
+
+template <bool GATE_UP, bool DIRECT>
+static void launch_skinny(const GemmKArgs &p, const GemmPlan &pl, hipStream_t s) {
+  if (pl.bm == 32) expert_gemm_skinny<1, GATE_UP, DIRECT><<<pl.grid, 256, 0, s>>>(p);
+  else expert_gemm_skinny<2, GATE_UP, DIRECT><<<pl.grid, 256, 0, s>>>(p);
 }
 
 // ---------------------------------------------------------------------------
@@ -1281,14 +1302,18 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
     *dn = GemmPlan{bm, cols, 1, mt * (d / cols), kGemmSimt};
     return;
   }
-  // Few rows per retained expert (decode): skinny 32x64 tiles stream the weights
-  // through many small workgroups; otherwise 128x128 tiles.  The gate/up
-  // projection takes 128-row tiles once the experts hold more than about 24
-  // rows each, even where those tiles do not cover the CUs: skinny tiles then
-  // read the weights of a busy expert more than once (Qwen3-shaped decode, 128
-  // tokens on a pool of 16: 80.8 against 85.6 us per layer).
-  const bool sk_shapes = inter % 128 == 0 && d % 64 == 0;
-  const bool gu_skinny = sk_shapes && rows <= 24 * active;
+  // Few rows per retained expert (decode): skinny tiles stream the weights through
+  // many small workgroups; otherwise 128-column tiles.  The gate/up projection
+  // takes 128-row tiles once the experts hold more than about 24 rows each, even
+  // where those tiles do not cover the CUs (GLM-shaped, 256 tokens on a static
+  // pool of 64, 32 rows each: 255 against 273 us on skinny tiles).  64-row skinny
+  // tiles from 12 rows on average, where groups of more than 32 rows appear and
+  // 32-row tiles would read their weights twice (the same batch's down: 174 ->
+  // 162 us; 1237 tokens, K' = 3: 354 -> 338); below, three workgroups of 32-row
+  // tiles a CU (Qwen3-shaped, one token: 54.9 against 56.4 us).  d is a multiple
+  // of 128; a reduction shorter than one skinny stage (I = 64) takes the tile.
+  const bool gu_skinny = rows <= 24 * active;
+  const int sk_m = rows <= 12 * active ? 32 : 64;
   // Many rows per retained expert (prefill, at least 128 on average): wide
   // tiles.  With the 128-row tail tiles a skewed load pays at most half a tile
   // per group: the Qwen3-shaped prefill (8192 tokens, K' = 4, 98 of 128 experts
@@ -1299,12 +1324,15 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   const bool gu_wide = !gu_skinny && inter % kWideBN == 0 && d % 128 == 0 && 2 * rows >= kWide * active &&
                        (long long)(rows / 128) * (inter / kWideBN) * 4 >= cu_count;
   // The down projection keeps skinny tiles up to about 48 rows per expert (at
-  // 64, 128x128 tiles: Qwen3-shaped decode, 256 tokens on a pool of 32, 115
-  // against 125 us per layer).
-  const bool dn_skinny = sk_shapes && rows <= 48 * active;
+  // 64, 128-column tiles: Qwen3-shaped decode, 512 tokens on a pool of 64, 51
+  // against 66 us), then 64-row tiles up to 80 (the same batch: 51 against 59 us
+  // on 128-row tiles, whose second half is padding and takes LDS from a third
+  // workgroup; gate/up is not faster on them: 98 against 92 us).
+  const bool dn_skinny = inter >= kSkK && rows <= 48 * active;
+  const int tile_m = rows <= 80 * active ? 64 : 128;
   if (gu_skinny) {
-    *gu = GemmPlan{kSkM, kSkN, 1, 0, kGemmSkinny};
-    gu->grid = (rows / kSkM + groups) * (inter / (kSkN / 2));  // >= sum of ceil(rows_g / 32) tiles
+    *gu = GemmPlan{sk_m, kSkN, 1, 0, kGemmSkinny};
+    gu->grid = (rows / sk_m + groups) * (inter / (kSkN / 2));  // >= sum of ceil(rows_g / bm) tiles
   } else if (gu_wide) {
     // tile list in 128-row units, one tile per unit and pair of 128-column
     // n-tiles; whole rounds plus the split remainder: at most that + one round
@@ -1329,9 +1357,9 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   // range keeps at least kMinSplitStages stages (an intermediate size of 768
   // split three ways ran 3 us slower per decode layer than unsplit, a 14336
   // one split in two 20 us faster).
-  const int bm = dn_skinny ? kSkM : 128;
+  const int bm = dn_skinny ? sk_m : tile_m;
   const int bn = dn_skinny ? kSkN : 128;
-  const int kk = dn_skinny ? kSkK : kBK, fill = dn_skinny ? 3 : 2;
+  const int kk = dn_skinny && inter % 128 == 0 ? 128 : kBK, fill = dn_skinny ? 3 : 2;
   *dn = GemmPlan{bm, bn, 1, 0, dn_skinny ? kGemmSkinny : kGemmTile};
   const int mt_expect = (rows + bm - 1) / bm > active ? (rows + bm - 1) / bm : active;
   const int dn_tiles = mt_expect * (d / bn);
@@ -1400,13 +1428,13 @@ hipError_t launch_expert_gemms(const ExpertArgs &a, const GemmPlan &gu, const Ge
   }
   if (gu.grid > 0) {
     if (gu.kind == kGemmSkinny) {
-      expert_gemm_skinny<true, false><<<gu.grid, 256, 0, s>>>(ga);
+      launch_skinny<true, false>(ga, gu, s);
     } else if (gu.kind == kGemmWide) {
       ga.P = a.wide_part;
       expert_gate_up_wide<<<gu.grid, 64 * kWideWaves, 0, s>>>(ga, gu.wgs);
       expert_wide_fixup<true, false><<<dim3(gu.wgs / 2, kWide / 16), 256, 0, s>>>(ga, gu.wgs);
     } else {
-      expert_gemm_tile<128, 128, 2, true, false><<<gu.grid, 256, 0, s>>>(ga);
+      expert_gemm_tile<128, 128, true, false><<<gu.grid, 256, 0, s>>>(ga);
     }
   }
   if (ev_mid) (void)hipEventRecord(ev_mid, s);
@@ -1423,14 +1451,18 @@ hipError_t launch_expert_gemms(const ExpertArgs &a, const GemmPlan &gu, const Ge
       }
     } else if (dn.kind == kGemmSkinny) {
       if (a.direct)
-        expert_gemm_skinny<false, true><<<dn.grid, 256, 0, s>>>(da);
+        launch_skinny<false, true>(da, dn, s);
       else
-        expert_gemm_skinny<false, false><<<dn.grid, 256, 0, s>>>(da);
+        launch_skinny<false, false>(da, dn, s);
     } else {
-      if (a.direct)
-        expert_gemm_tile<128, 128, 2, false, true><<<dn.grid, 256, 0, s>>>(da);
+      if (dn.bm == 64 && a.direct)
+        expert_gemm_tile<64, 128, false, true><<<dn.grid, 256, 0, s>>>(da);
+      else if (dn.bm == 64)
+        expert_gemm_tile<64, 128, false, false><<<dn.grid, 256, 0, s>>>(da);
+      else if (a.direct)
+        expert_gemm_tile<128, 128, false, true><<<dn.grid, 256, 0, s>>>(da);
       else
-        expert_gemm_tile<128, 128, 2, false, false><<<dn.grid, 256, 0, s>>>(da);
+        expert_gemm_tile<128, 128, false, false><<<dn.grid, 256, 0, s>>>(da);
     }
   }
   return hipGetLastError();
@@ -1460,7 +1492,7 @@ hipError_t launch_plain_gemm_nt(const void *A, const void *W, int M, int N, int 
   g.kc = K / P;
   g.Y = part;
   const int grid = (M + 127) / 128 * g.n_tiles * P;
-  expert_gemm_tile<128, 128, 2, false, false, true><<<grid, 256, 0, s>>>(g);
+  expert_gemm_tile<128, 128, false, false, true><<<grid, 256, 0, s>>>(g);
   return hipGetLastError();
 }
 

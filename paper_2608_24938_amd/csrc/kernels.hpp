@@ -97,7 +97,7 @@ hipError_t launch_static_pool(const float *h, int N, int D, const float *S, cons
                               hipStream_t s);
 
 // ---- expert GEMMs and combine (k_gemm.hip) ----
-// kGemmSimt: float32 layers (16 to 64 rows x 16 or 32 columns); kGemmTile: 128x128 tiles; kGemmSkinny: 32x64 tiles for few rows per expert;
+// kGemmSimt: float32 layers (16 to 64 rows x 16 or 32 columns); kGemmTile: 128x128 or 64x128 tiles; kGemmSkinny: 32x64 or 64x64 tiles for few rows per expert;
 // kGemmWide: 256x256 tiles (eight waves, loads straight into LDS) in rounds of
 // `wgs` workgroups, a short last round split along the reduction.
 enum { kGemmSimt = 0, kGemmTile = 1, kGemmSkinny = 2, kGemmWide = 3 };

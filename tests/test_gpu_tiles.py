@@ -119,3 +119,20 @@ def test_wide_tile_edges(d, inter, k):
     assert X.lib().exfold_gemm_plan(ctypes.byref(lp), ids.size, len(sizes), 256, plan) == X.OK
     assert plan[0] == 3 and plan[5] == (3 if d % 512 == 0 else 1)
     assert _execute(shape, ids.shape[0], ids, seed=4) <= TOL_Y["bf16"]
+
+
+# Skinny tiles of 32 and 64 rows (up to 12 and up to 24 gate/up or 48 down rows per busy expert) and
+# 64-row down tiles (up to 80): groups of 0, 1, 32, 33, 64, 65 and more rows; reductions that end
+# in half a 128-column stage (I = 192, 320, 704), of one stage (I = 128) and below one (I = 64); one and
+# several routes a token, the shared expert, a split down reduction (I = 4096, few tiles).
+@pytest.mark.parametrize("d,inter,sizes,k,shared", [
+    (256, 192, [1, 0, 32, 33, 0, 2, 4, 0], 1, 0), (256, 192, [1, 0, 12, 33, 0, 24, 9, 1], 2, 192),
+    (128, 320, [64, 65, 0, 32, 33, 1, 3, 2], 1, 0), (384, 704, [64, 65, 0, 32, 33, 1, 3, 2], 2, 0),
+    (128, 128, [40, 30, 20, 60], 2, 128), (256, 64, [20, 10, 5, 1], 1, 0), (256, 64, [20, 10, 5, 1], 2, 0),
+    (256, 320, [64, 65, 63, 128, 129, 1], 2, 0), (640, 192, [64, 65, 63, 128, 20, 1], 1, 0),
+    (128, 4096, [3, 1, 0, 4], 2, 0), (128, 4160, [40, 50, 33, 65], 2, 0)])
+def test_streaming_tile_edges(d, inter, sizes, k, shared):
+    ids = np.random.default_rng(inter).permutation(np.repeat(np.arange(len(sizes)), sizes)).astype(np.int32)
+    ids = ids[: len(ids) // k * k].reshape(-1, k)
+    shape = _shape(d, inter, len(sizes), k, dtype="bf16", shared=shared)
+    assert _execute(shape, ids.shape[0], ids, seed=5) <= TOL_Y["bf16"]
