@@ -1323,12 +1323,16 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   // 48 wide tiles: 130.8 against 103.8 us per layer).
   const bool gu_wide = !gu_skinny && inter % kWideBN == 0 && d % 128 == 0 && 2 * rows >= kWide * active &&
                        (long long)(rows / 128) * (inter / kWideBN) * 4 >= cu_count;
-  // The down projection keeps skinny tiles up to about 48 rows per expert (at
-  // 64, 128-column tiles: Qwen3-shaped decode, 512 tokens on a pool of 64, 51
-  // against 66 us), then 64-row tiles up to 80 (the same batch: 51 against 59 us
-  // on 128-row tiles, whose second half is padding and takes LDS from a third
-  // workgroup; gate/up is not faster on them: 98 against 92 us).
-  const bool dn_skinny = inter >= kSkK && rows <= 48 * active;
+  // The down projection keeps skinny tiles up to about 48 rows per expert, or to
+  // 20 where there are more than two 128-column tiles a CU: then 64-row tiles of
+  // 128 columns (three workgroups a CU) stream as well and fetch the rows of H
+  // half as often (GLM-shaped, 256 tokens on a static pool of 64, 32 rows each:
+  // 149 against 163 us; 700 Qwen3-shaped prefill tokens, K' = 4: 61 against 71;
+  // at 18 rows, 64 tokens on a pool of 32, 75 against 73).  64-row tiles up to 80
+  // rows (512 Qwen3-shaped tokens on a pool of 64: 51 us against 66 on skinny and
+  // 59 on 128-row tiles, whose second half is padding there; gate/up is not
+  // faster on them: 98 against 92 us).
+  const bool dn_skinny = inter >= kSkK && rows <= (active * (d / 128) > 2 * cu_count ? 20 : 48) * active;
   const int tile_m = rows <= 80 * active ? 64 : 128;
   if (gu_skinny) {
     *gu = GemmPlan{sk_m, kSkN, 1, 0, kGemmSkinny};

@@ -130,9 +130,46 @@ def test_wide_tile_edges(d, inter, k):
     (128, 320, [64, 65, 0, 32, 33, 1, 3, 2], 1, 0), (384, 704, [64, 65, 0, 32, 33, 1, 3, 2], 2, 0),
     (128, 128, [40, 30, 20, 60], 2, 128), (256, 64, [20, 10, 5, 1], 1, 0), (256, 64, [20, 10, 5, 1], 2, 0),
     (256, 320, [64, 65, 63, 128, 129, 1], 2, 0), (640, 192, [64, 65, 63, 128, 20, 1], 1, 0),
-    (128, 4096, [3, 1, 0, 4], 2, 0), (128, 4160, [40, 50, 33, 65], 2, 0)])
+    (128, 4096, [3, 1, 0, 4], 2, 0), (128, 4160, [40, 50, 33, 65], 2, 0),
+    # more than two 128-column down tiles a CU: 64-row tiles from 21 rows on average, skinny at 20
+    (2048, 128, [21] * 33, 1, 0), (2048, 192, [20] * 33, 1, 0), (4096, 64, [64, 1, 0, 65, 33] * 7, 2, 0)])
 def test_streaming_tile_edges(d, inter, sizes, k, shared):
     ids = np.random.default_rng(inter).permutation(np.repeat(np.arange(len(sizes)), sizes)).astype(np.int32)
     ids = ids[: len(ids) // k * k].reshape(-1, k)
     shape = _shape(d, inter, len(sizes), k, dtype="bf16", shared=shared)
     assert _execute(shape, ids.shape[0], ids, seed=5) <= TOL_Y["bf16"]
+
+
+# One-workgroup permutation and decode front end: up to 1, 4 and 8 slots a thread (either side of 1024
+# and 4096 slots, the largest), a last wave with one slot, one expert with every slot, 256 experts.
+@pytest.mark.parametrize("T,K,n,phase", [(1, 1, 3, "execute"), (65, 1, 256, "execute"), (128, 8, 128, "execute"),
+                                         (1025, 1, 7, "execute"), (1024, 4, 256, "execute"),
+                                         (128, 8, 128, "decode"), (129, 8, 40, "decode"), (512, 8, 64, "decode"),
+                                         (513, 8, 64, "decode"), (512, 16, 256, "decode"), (1024, 8, 9, "decode"),
+                                         (16, 16, 256, "decode"), (17, 2, 128, "decode")])
+def test_one_workgroup_permutation(T, K, n, phase):
+    shape = _shape(128, 64, n, K, dtype="bf16", bias=True)
+    lp = LayerPair(shape, seed=n + K)
+    x = to_dev(synth.tokens(shape, T, seed=n))
+    print(f"permutation: T={T} K={K} N={n} {phase}", flush=True)
+    if phase == "execute":
+        ids = np.zeros((T, K), np.int32) if n == 7 else _skewed(T, K, n, T)
+        dbg = {"offsets": torch.empty(n + 2, dtype=torch.int32, device="cuda:0"),
+               "row_slot": torch.empty(T * K, dtype=torch.int32, device="cuda:0")}
+        X.moe_execute(lp.dev, x, to_dev(ids), to_dev(np.ones((T, K), np.float32)), debug=dbg)
+    else:
+        S, L, h = synth.synthetic_tables(n, seed=n)
+        budget = max(2, n // 4)
+        dbg = X.debug_buffers(lp.dev, T, phase, budget, "cuda:0")
+        X.moe_forward(lp.dev, x, phase, budget, to_dev(S), to_dev(L), to_dev(h), debug=dbg)
+    sync()
+    g = {k: v.cpu().numpy() for k, v in dbg.items()}
+    if phase == "decode":
+        pool, _ = O.select_decode_pool(g["topk_ids"], g["topk_w"], h, n, budget)
+        assert g["pool"][: int(g["pool_size"][0])].tolist() == pool
+        ids, f_w, _, _ = O.fold_decode(g["topk_ids"], g["topk_w"], pool, S, L, n)
+        np.testing.assert_array_equal(g["fold_ids"], ids)
+        np.testing.assert_array_equal(g["fold_w"].view(np.uint32), f_w.view(np.uint32))
+    _, offsets, row_slot = O.permute_routes(ids, n)
+    np.testing.assert_array_equal(g["offsets"][: n + 1], offsets)
+    np.testing.assert_array_equal(g["row_slot"], row_slot)
