@@ -1060,7 +1060,10 @@ constexpr int kFrontWaves = kPoolThreads / kWave;
 constexpr int kFrontPfN = 32;
 constexpr int kFrontPfCols = (kFrontPfN * kFrontPfN + kPoolThreads - 1) / kPoolThreads;
 constexpr int kFrontScanWaves = (kMaxExperts + 2 + kWave - 1) / kWave;
+constexpr int kFrontFusedTokens = kFrontWaves;  // batches whose Top-K runs in the front end
 
+// STEPS: slots per thread at most; FUSED: Top-K and softmax here, from lpart.
+template <int STEPS, bool FUSED>
 __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
     const int32_t *__restrict__ ids, const float *__restrict__ w, int B, int N, int K, int D,
     const float *__restrict__ h, const float *__restrict__ S, const float *__restrict__ L,
@@ -1072,8 +1075,9 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
     const int32_t *__restrict__ static_tgt, const float *__restrict__ static_scl, int identity,
     const float *__restrict__ lpart, int lP, const float *__restrict__ bias,
     float *__restrict__ logits_out, int32_t *__restrict__ ids_out, float *__restrict__ w_out) {
-  __shared__ uint8_t sid[kDecodeFrontMaxSlots];   // expert of each slot (N <= 256)
-  __shared__ float sw[kDecodeFrontMaxSlots];      // its weight
+  // routes found here (fused Top-K), handed to the threads that own the slots
+  __shared__ uint8_t sid[FUSED ? kFrontFusedTokens * kMaxTopK : 1];
+  __shared__ float sw[FUSED ? kFrontFusedTokens * kMaxTopK : 1];
   __shared__ unsigned long long wsum[kMaxExperts];
   __shared__ int cnt[kMaxExperts];
   __shared__ double score[kMaxExperts];
@@ -1081,10 +1085,8 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
   __shared__ int in_pool[kMaxExperts];
   __shared__ int tgt[kMaxExperts];
   __shared__ float scl[kMaxExperts];
-  __shared__ int rows_of[kMaxExperts];  // executed rows per routed expert
   __shared__ int rank_sh[kMaxExperts];
-  __shared__ int cur[kMaxExperts];
-  __shared__ int wcnt[kFrontWaves][kMaxExperts];
+  __shared__ int wcnt[kFrontWaves][kMaxExperts];  // slots per wave and target, then each wave's first row
   __shared__ unsigned long long best[kMaxExperts];
   __shared__ int scan_part[3 * kFrontScanWaves];
   __shared__ int cand[kMaxExperts];
@@ -1115,8 +1117,9 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
     wsum[tid] = 0ull;
     cnt[tid] = 0;
     in_pool[tid] = 0;
-    rows_of[tid] = 0;
     rank_sh[tid] = 0;
+#pragma unroll
+    for (int q = 0; q < kFrontWaves; ++q) wcnt[q][tid] = 0;
     if (identity) {
       tgt[tid] = tid;
       scl[tid] = 1.0f;
@@ -1129,36 +1132,49 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
       in_pool[tid] = te == tid;
     }
   }
+  // Slot lo + 64 s + lane of the wave's run of `per` slots lives in this thread's
+  // registers (its expert and weight), so remap, ranking and scatter need no
+  // exchange: the runs are in slot order, wave after wave.
+  const int per = (slots + kPoolThreads - 1) / kPoolThreads * kWave, lo = wave * per;
+  int re[STEPS];
+  float rw[STEPS];
+#define EXF_FRONT_STEPS(s_) \
+  _Pragma("unroll") for (int s_ = 0; s_ < STEPS; ++s_) if (kWave * s_ < per)
+  if constexpr (!FUSED) {
+    EXF_FRONT_STEPS(s) {
+      const int j = lo + kWave * s + lane;
+      re[s] = j < slots ? clamp_id(ids[j], N) : 0;
+      rw[s] = j < slots ? w[j] : 0.f;
+    }
+  }
   lds_barrier();
 
   // ---- pool (Eq. decode_budget): exact fixed-point weight sums ----
-  auto add_slot = [&](int j, int e, float wv) {
-    sid[j] = (uint8_t)e;
-    sw[j] = wv;
+  auto add_slot = [&](int e, float wv) {
     atomicAdd(&cnt[e], 1);
-    if (dynamic) {
-      const long long q = __double2ll_rn((double)wv * 1099511627776.0);  // 2^40
-      atomicAdd(&wsum[e], (unsigned long long)q);
-    }
+    const long long q = __double2ll_rn((double)wv * 1099511627776.0);  // 2^40
+    atomicAdd(&wsum[e], (unsigned long long)q);
   };
-  if (lpart) {
-    // Top-K and softmax of the batch here (small batches): wave w takes tokens
-    // w, w + kFrontWaves, ... with the per-token steps of route_tokens_kernel
-    for (int t = wave; t < B; t += kFrontWaves) {
+  if constexpr (FUSED) {
+    // Top-K and softmax of the batch here (small batches): wave w takes token w by
+    // the per-token steps of route_tokens_kernel
+    if (wave < B) {
       float v[4];
-      wave_logit_row(lpart, lP, B, N, bias, t, lane, logits_out, v);
+      wave_logit_row(lpart, lP, B, N, bias, wave, lane, logits_out, v);
       int my_id = 0;
       float my_w = 0.f;
       wave_topk_softmax(v, N, K, lane, my_id, my_w);
       if (lane < K) {
-        const int j = t * K + lane;
+        const int j = wave * K + lane;
         ids_out[j] = my_id;
         w_out[j] = my_w;
-        add_slot(j, my_id, my_w);
+        sid[j] = (uint8_t)my_id;
+        sw[j] = my_w;
+        if (dynamic) add_slot(my_id, my_w);
       }
     }
-  } else {
-    for (int j = tid; j < slots; j += kPoolThreads) add_slot(j, clamp_id(ids[j], N), w[j]);
+  } else if (dynamic) {
+    EXF_FRONT_STEPS(s) if (lo + kWave * s + lane < slots) add_slot(re[s], rw[s]);
   }
 #pragma unroll
   for (int b = 0; b < kFrontPfCols; ++b) {
@@ -1253,39 +1269,66 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
   }  // dynamic
   lds_barrier();
 
-  // executed rows per target: the slots of its sources
-  if (tid < N && cnt[tid] > 0) atomicAdd(&rows_of[tgt[tid]], cnt[tid]);
-  // ---- remap every slot (Eq. decode_remap); retained slots copied ----
-  for (int j = tid; j < slots; j += kPoolThreads) {
-    const int e = sid[j];
-    const float wv = sw[j];
+  // ---- remap every slot (Eq. decode_remap; retained slots copied) and rank it
+  // among the wave's slots of its target, in slot order ----
+  int rank[STEPS];
+  EXF_FRONT_STEPS(s) {
+    const int j = lo + kWave * s + lane;
+    const bool valid = j < slots;
+    if (FUSED && valid) {
+      re[s] = sid[j];
+      rw[s] = sw[j];
+    }
+    const int e = valid ? re[s] : 0;
     const int te = tgt[e];
-    const float wn = in_pool[e] ? wv : wv * scl[e];
-    if (!identity) {
+    const float wn = in_pool[e] ? rw[s] : rw[s] * scl[e];
+    if (!identity && valid) {
       out_ids[j] = te;
       out_w[j] = wn;
     }
-    sid[j] = (uint8_t)te;
-    sw[j] = wn;
+    re[s] = te;
+    rw[s] = wn;
+    // lanes of this wave with the same target (8 ballots: N <= 256)
+    uint64_t m = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+      const bool set = (te >> bit) & 1;
+      const uint64_t bal = __ballot(set);
+      m &= set ? bal : ~bal;
+    }
+    const int before = __popcll(m & lanemask_lt(lane));
+    const int seen = wcnt[wave][te];  // of the wave's earlier steps (its own LDS accesses stay in order)
+    rank[s] = seen + before;
+    if (valid && before == 0) wcnt[wave][te] = seen + __popcll(m);
   }
   lds_barrier();
 
   // ---- group offsets and GEMM m-tile lists: one group per thread ----
   {
+    int c[kFrontWaves], rows = 0;
+    if (tid < N) {
+#pragma unroll
+      for (int q = 0; q < kFrontWaves; ++q) c[q] = wcnt[q][tid];
+#pragma unroll
+      for (int q = 0; q < kFrontWaves; ++q) rows += c[q];
+    }
     int v[3] = {0, 0, 0};
     if (tid < groups) {
-      const int r = tid < N ? rows_of[tid] : t_shared;
+      const int r = tid < N ? rows : t_shared;
       v[0] = r;
       v[1] = (r + bm0 - 1) / bm0;
       v[2] = (r + bm1 - 1) / bm1;
     }
-    for (int e = tid; e < N; e += kPoolThreads) {
-#pragma unroll
-      for (int q = 0; q < kFrontWaves; ++q) wcnt[q][e] = 0;
-    }
     int ex[3], tot[3];
     block_scan3<kFrontScanWaves>(v, ex, tot, scan_part);
-    if (tid < N) cur[tid] = ex[0];  // group start (routed experts)
+    if (tid < N) {  // first row of each wave's slots of the group
+      int first = ex[0];
+#pragma unroll
+      for (int q = 0; q < kFrontWaves; ++q) {
+        wcnt[q][tid] = first;
+        first += c[q];
+      }
+    }
     if (tid < N + 2) {
       offsets[tid] = (tid < N) ? ex[0] : (tid == N) ? slots : slots + t_shared;
       tile_start0[tid] = (tid < groups) ? ex[1] : tot[1];
@@ -1294,42 +1337,18 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
   }
   lds_barrier();
 
-  // ---- stable scatter: rounds of kPoolThreads slots in slot order ----
-  for (int base = 0; base < slots; base += kPoolThreads) {
-    const int j = base + tid;
-    const bool valid = j < slots;
-    const int e = valid ? (int)sid[j] : 0;
-    // lanes of this wave with the same expert (8 ballots: N <= 256)
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const bool set = (e >> bit) & 1;
-      const uint64_t bal = __ballot(set);
-      m &= set ? bal : ~bal;
-    }
-    const int rank = __popcll(m & lanemask_lt(lane));
-    if (valid && rank == 0) wcnt[wave][e] = __popcll(m);
-    lds_barrier();
-    if (valid) {
-      int pos = cur[e] + rank;
-      for (int q = 0; q < wave; ++q) pos += wcnt[q][e];
+  // ---- stable scatter ----
+  EXF_FRONT_STEPS(s) {
+    const int j = lo + kWave * s + lane;
+    if (j < slots) {
+      const int pos = wcnt[wave][re[s]] + rank[s];
       row_slot[pos] = j;
       row_token[pos] = j / K;
-      row_w[pos] = sw[j];
+      row_w[pos] = rw[s];
       slot_row[j] = pos;
     }
-    lds_barrier();
-    for (int x = tid; x < N; x += kPoolThreads) {
-      int add = 0;
-#pragma unroll
-      for (int q = 0; q < kFrontWaves; ++q) {
-        add += wcnt[q][x];
-        wcnt[q][x] = 0;
-      }
-      cur[x] += add;
-    }
-    lds_barrier();
   }
+#undef EXF_FRONT_STEPS
   // Shared-expert rows follow the routed rows, one per token, weight 1.
   for (int i = tid; i < t_shared; i += kPoolThreads) {
     row_token[slots + i] = i;
@@ -1338,39 +1357,44 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
   }
 }
 
+// The build for this many slots (slots handed in).
+static auto front_kernel(int slots) {
+  static_assert(8 * kPoolThreads == kDecodeFrontMaxSlots, "slots per thread");
+  static_assert(kFrontFusedTokens * kMaxTopK <= kPoolThreads, "the fused front holds one slot a thread");
+  return slots <= kPoolThreads ? decode_front_kernel<1, false>
+         : slots <= 4 * kPoolThreads ? decode_front_kernel<4, false> : decode_front_kernel<8, false>;
+}
+
 hipError_t launch_decode_front(const int32_t *ids, const float *w, int B, int N, int K, int D,
                                const float *h, const float *S, const float *L, int32_t *pool,
                                int32_t *pool_size, int32_t *out_ids, float *out_w, int32_t *tgt,
                                float *scl, int t_shared, int bm0, int bm1, const PermBuffers &pb,
                                const int32_t *static_tgt, const float *static_scl, hipStream_t s,
                                const FrontTopK &fused) {
-  decode_front_kernel<<<1, kPoolThreads, 0, s>>>(ids, w, B, N, K, D, h, S, L, pool, pool_size, out_ids,
-                                                 out_w, tgt, scl, t_shared, bm0, bm1, pb.offsets,
-                                                 pb.tile_start0, pb.tile_start1, pb.row_token,
-                                                 pb.row_slot, pb.row_w, pb.slot_row, static_tgt,
-                                                 static_scl, 0, fused.part, fused.P, fused.bias,
-                                                 fused.logits_out, fused.ids_out, fused.w_out);
+  const auto kernel = fused.part ? decode_front_kernel<1, true> : front_kernel(B * K);
+  kernel<<<1, kPoolThreads, 0, s>>>(ids, w, B, N, K, D, h, S, L, pool, pool_size, out_ids, out_w, tgt, scl,
+                                    t_shared, bm0, bm1, pb.offsets, pb.tile_start0, pb.tile_start1,
+                                    pb.row_token, pb.row_slot, pb.row_w, pb.slot_row, static_tgt, static_scl,
+                                    0, fused.part, fused.P, fused.bias, fused.logits_out, fused.ids_out,
+                                    fused.w_out);
   return hipGetLastError();
 }
 
-// One token per wave: with two, the second token's partial-logit loads wait
-// behind the first (32 tokens of the Mixtral-shaped layer: 16.7 us fused
-// against 5.2 + 8.4 us in two launches; one token of the Qwen3-shaped layer:
-// 12.5 us against 4.8 + 9.1 us).
+// One token per wave: with two side by side, the one CU's SIMDs hold eight
+// selections each and the front end takes longer than the launch it saves (32
+// tokens of the Qwen3-shaped layer: 20.0 us against 16.4 for the two kernels).
 bool decode_front_fuses_topk(int B, int N) {
   (void)N;
-  return B <= kFrontWaves;
+  return B <= kFrontFusedTokens;
 }
 
 hipError_t launch_permute_one_block(const int32_t *ids, const float *w, int T, int k_out, int N,
                                     int t_shared, int bm0, int bm1, const PermBuffers &pb,
                                     hipStream_t s) {
-  decode_front_kernel<<<1, kPoolThreads, 0, s>>>(ids, w, T, N, k_out, N, nullptr, nullptr, nullptr,
-                                                 nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                 t_shared, bm0, bm1, pb.offsets, pb.tile_start0,
-                                                 pb.tile_start1, pb.row_token, pb.row_slot, pb.row_w,
-                                                 pb.slot_row, nullptr, nullptr, 1, nullptr, 0,
-                                                 nullptr, nullptr, nullptr, nullptr);
+  front_kernel(T * k_out)<<<1, kPoolThreads, 0, s>>>(
+      ids, w, T, N, k_out, N, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+      t_shared, bm0, bm1, pb.offsets, pb.tile_start0, pb.tile_start1, pb.row_token, pb.row_slot, pb.row_w,
+      pb.slot_row, nullptr, nullptr, 1, nullptr, 0, nullptr, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 
