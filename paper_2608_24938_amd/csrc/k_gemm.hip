@@ -680,10 +680,9 @@ __device__ __forceinline__ void store4_bf16_nt(bf16_t *dst, float a, float b, fl
   __builtin_nontemporal_store(*reinterpret_cast<const u32x2 *>(&v), reinterpret_cast<u32x2 *>(dst));
 }
 
-// Finished tile: gate/up writes H = SiLU(gate) * up; down writes y (direct)
-// or fp32 rows Y scaled by the row's routing weight, or unscaled bf16 rows Yh
-// (the combine applies the weight).
-template <bool GATE_UP, bool DIRECT, bool DBL>
+// Finished tile, from the registers: gate/up writes H = SiLU(gate) * up, the
+// direct down projection y, scaled by the row's routing weight.
+template <bool GATE_UP, bool DBL>
 __device__ __forceinline__ void wide_store(const GemmKArgs &p, const TileId &t, int row0, int valid,
                                            const f32x16 (&acc)[kWideTM][kWideTN]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -702,42 +701,31 @@ __device__ __forceinline__ void wide_store(const GemmKArgs &p, const TileId &t, 
         store4_bf16(dst + 8 * g, silu(gt[4 * g]) * up[4 * g], silu(gt[4 * g + 1]) * up[4 * g + 1],
                     silu(gt[4 * g + 2]) * up[4 * g + 2], silu(gt[4 * g + 3]) * up[4 * g + 3]);
     } else {
-      const float w = p.Yh && !DIRECT ? 1.f : p.row_w[row];
-      const int n0 = t.nt * kWideBN + c4;
-      const long long base = DIRECT ? (long long)p.row_token[row] * p.d : (long long)row * p.d;
+      const float w = p.row_w[row];
+      bf16_t *dst = p.y + (long long)p.row_token[row] * p.d + t.nt * kWideBN + c4;
 #pragma unroll
       for (int j = 0; j < kWideTN; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x16 &c = acc[i][j];
-          const int n = n0 + wide_col<DBL>(wn, i, j) + 8 * g;
-          const float v0 = c[4 * g] * w, v1 = c[4 * g + 1] * w, v2 = c[4 * g + 2] * w, v3 = c[4 * g + 3] * w;
-          if (DIRECT)
-            store4_bf16_nt(p.y + base + n, v0, v1, v2, v3);
-          else if (p.Yh)
-            store4_bf16(p.Yh + base + n, v0, v1, v2, v3);
-          else
-            *reinterpret_cast<float4 *>(p.Y + ((long long)t.ks * p.rows + row) * p.d + n) =
-                make_float4(v0, v1, v2, v3);
+          store4_bf16_nt(dst + wide_col<DBL>(wn, i, j) + 8 * g, c[4 * g] * w, c[4 * g + 1] * w, c[4 * g + 2] * w,
+                         c[4 * g + 3] * w);
         }
     }
   }
 }
 
-// Finished bf16 tile through LDS (the ring is free after the main loop): each
-// lane writes its runs of four columns (SiLU(gate) * up, or the down output,
-// scaled by the row's routing weight only when it goes straight to y) into a
-// row-major bf16 tile, and the
-// workgroup then stores whole rows 16 bytes a lane, so one store instruction
-// covers a few complete rows instead of 32 scattered 16-byte pieces.  Taken
-// for the bf16 rows of the down projection (Qwen3-shaped prefill: down 200 ->
-// 177 us); for H and the direct y it cost more than it saved (the extra path
-// spills scalar registers in those kernels).
-template <bool GATE_UP, bool DIRECT, int NW, bool DBL>
+// Finished bf16 rows of the down projection through LDS (the ring is free after
+// the main loop): each lane writes its runs of four columns into a row-major
+// bf16 tile, and the workgroup then stores whole rows 16 bytes a lane, so one
+// store instruction covers a few complete rows instead of 32 scattered 16-byte
+// pieces (Qwen3-shaped prefill: down 200 -> 177 us).  For H and the direct y it
+// gains nothing.
+template <bool DBL>
 __device__ __forceinline__ void wide_store_lds(const GemmKArgs &p, const TileId &t, int row0, int valid,
                                                const f32x16 (&acc)[kWideTM][kWideTN], bf16_t *smem) {
   constexpr int BM = DBL ? kWide / 2 : kWide;
-  constexpr int COLS = (DBL ? 2 : 1) * kWideBN / (GATE_UP ? 2 : 1);  // output columns of the tile
+  constexpr int COLS = (DBL ? 2 : 1) * kWideBN;               // output columns of the tile
   constexpr int PITCH = COLS * 2 + 16;                        // LDS bytes per row (padded)
   static_assert(BM * PITCH <= kWideSmemElems * 2, "staging tile fits the ring");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -746,45 +734,24 @@ __device__ __forceinline__ void wide_store_lds(const GemmKArgs &p, const TileId 
   char *lds = reinterpret_cast<char *>(smem);
 #pragma unroll
   for (int i = 0; i < kWideTM; ++i) {
-    const int ml = wide_row<DBL>(wm, i) + (lane & 31);
-    const float w = (!GATE_UP && DIRECT && ml < valid) ? p.row_w[row0 + ml] : 1.f;
-    bf16_t *rowp = reinterpret_cast<bf16_t *>(lds + ml * PITCH) + c4;
-    if (GATE_UP) {
-      const f32x16 &gt = acc[i][0], &up = acc[i][1];
+    bf16_t *rowp = reinterpret_cast<bf16_t *>(lds + (wide_row<DBL>(wm, i) + (lane & 31)) * PITCH) + c4;
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        store4_bf16(rowp + wide_pair_col<DBL>(wn, i) + 8 * g, silu(gt[4 * g]) * up[4 * g],
-                    silu(gt[4 * g + 1]) * up[4 * g + 1], silu(gt[4 * g + 2]) * up[4 * g + 2],
-                    silu(gt[4 * g + 3]) * up[4 * g + 3]);
-    } else {
+    for (int j = 0; j < kWideTN; ++j)
 #pragma unroll
-      for (int j = 0; j < kWideTN; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x16 &c = acc[i][j];
-          store4_bf16(rowp + wide_col<DBL>(wn, i, j) + 8 * g, c[4 * g] * w, c[4 * g + 1] * w, c[4 * g + 2] * w,
-                      c[4 * g + 3] * w);
-        }
-    }
+      for (int g = 0; g < 4; ++g) {
+        const f32x16 &c = acc[i][j];
+        store4_bf16(rowp + wide_col<DBL>(wn, i, j) + 8 * g, c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
+      }
   }
   lds_barrier();
   constexpr int CPR = COLS / 8;                               // 16-byte chunks per row
-  for (int q = threadIdx.x; q < BM * CPR; q += 64 * NW) {
+  for (int q = threadIdx.x; q < BM * CPR; q += 64 * kWideWaves) {
     const int ml = q / CPR, ch = q % CPR;
     if (ml >= valid) continue;
-    const int row = row0 + ml;
-    const u32x4 v = *reinterpret_cast<const u32x4 *>(lds + ml * PITCH + ch * 16);
-    bf16_t *dst;
-    if (GATE_UP)
-      dst = p.H + (long long)row * p.inter + t.nt * (kWideBN / 2);
-    else if (DIRECT)
-      dst = p.y + (long long)p.row_token[row] * p.d + t.nt * kWideBN;
-    else
-      dst = p.Yh + (long long)row * p.d + t.nt * kWideBN;
-    *reinterpret_cast<u32x4 *>(dst + ch * 8) = v;
+    *reinterpret_cast<u32x4 *>(p.Yh + (long long)(row0 + ml) * p.d + t.nt * kWideBN + ch * 8) =
+        *reinterpret_cast<const u32x4 *>(lds + ml * PITCH + ch * 16);
   }
 }
-
 
 // ---------------------------------------------------------------------------
 // Wide-tile launches: whole rounds of tiles plus a split remainder.  With one
@@ -818,30 +785,49 @@ __device__ __forceinline__ WideSplit wide_split(const GemmKArgs &p, int G) {
   return WideSplit{total, 0, 1};
 }
 
-// Partial tile in the accumulator layout: row-major, 256 (DBL: 512) columns.
-template <bool DBL>
-__device__ __forceinline__ void wide_store_partial(float *P, const f32x16 (&acc)[kWideTM][kWideTN]) {
-  constexpr int BN = DBL ? 2 * kWideBN : kWideBN;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Finished float32 tile through LDS in two halves of 128 rows x 256 columns
+// (full tiles: the row halves; tails: the n-tiles), whole rows of 1 KiB a wave
+// instead of 32-byte pieces of 32 rows: row ml of half h goes to dst + ml * ld +
+// h * kWideBN (tails), scaled by scale(ml).  Kept rows of a calibration (4096
+// tokens x 8, d 2048): down 190 -> 170 us; split partials 1-3 us a launch.
+template <bool DBL, typename Scale>
+__device__ __forceinline__ void wide_store_f32(float *dst, long long ld, int valid, Scale scale,
+                                               const f32x16 (&acc)[kWideTM][kWideTN], bf16_t *smem) {
+  constexpr int PITCH = kWideBN * 4 + 16;  // LDS bytes per row (padded)
+  static_assert(kWide / 2 * PITCH <= kWideSmemElems * 2, "staging half fits the ring");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;
+  char *lds = reinterpret_cast<char *>(smem);
 #pragma unroll
-  for (int i = 0; i < kWideTM; ++i) {
-    float *prow = P + (wide_row<DBL>(wm, i) + (lane & 31)) * BN + 4 * (lane >> 5);
+  for (int h = 0; h < 2; ++h) {
+    if (h) lds_barrier();
 #pragma unroll
-    for (int j = 0; j < kWideTN; ++j)
+    for (int ib = 0; ib < 2; ++ib) {
+      const int i = 2 * h + ib, ml = wide_row<DBL>(wm, i) + (lane & 31);
+      const float w = scale(min(ml, valid - 1));
+      char *rowp = lds + (wide_row<true>(wm, i) + (lane & 31)) * PITCH + 16 * (lane >> 5);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x16 &c = acc[i][j];
-        *reinterpret_cast<float4 *>(prow + wide_col<DBL>(wn, i, j) + 8 * g) =
-            make_float4(c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]);
-      }
+      for (int j = 0; j < kWideTN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x16 &c = acc[i][j];
+          *reinterpret_cast<float4 *>(rowp + 4 * (wide_col<false>(wn, i, j) + 8 * g)) =
+              make_float4(c[4 * g] * w, c[4 * g + 1] * w, c[4 * g + 2] * w, c[4 * g + 3] * w);
+        }
+    }
+    lds_barrier();
+    for (int r = wave; r < kWide / 2; r += kWideWaves) {
+      const int ml = (DBL ? 0 : h * (kWide / 2)) + r;
+      if (ml >= valid) break;
+      const float4 v = *reinterpret_cast<const float4 *>(lds + r * PITCH + lane * 16);
+      *reinterpret_cast<float4 *>(dst + ml * ld + (DBL ? h * kWideBN : 0) + lane * 4) = v;
+    }
   }
 }
 
 // Workgroup blockIdx.x of a launch of ndp + rem s workgroups (more exit).
 template <bool GATE_UP, bool DIRECT>
 __device__ __forceinline__ void wide_gemm(const GemmKArgs &p, int G, bf16_t *smem) {
-  constexpr int NW = kWideWaves;
   const WideSplit w = wide_split(p, G);
   const int KT = p.kc / kWideBK;
   const int b = blockIdx.x;
@@ -863,6 +849,19 @@ __device__ __forceinline__ void wide_gemm(const GemmKArgs &p, int G, bf16_t *sme
   f32x16 acc[kWideTM][kWideTN];
   // the wave's 32-row blocks that hold rows of the group (wave-uniform)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // partial tile: row-major, 256 (tail: 512) columns
+#define EXF_W_STORE(DBL_)                                                                      \
+  do {                                                                                         \
+    if (part)                                                                                  \
+      wide_store_f32<DBL_>(part, (DBL_ ? 2 : 1) * kWideBN, valid, [](int) { return 1.f; }, acc, smem); \
+    else if (!GATE_UP && !DIRECT && p.Yh)                                                      \
+      wide_store_lds<DBL_>(p, t, row0, valid, acc, smem);                                      \
+    else if (!GATE_UP && !DIRECT)                                                              \
+      wide_store_f32<DBL_>(p.Y + (long long)row0 * p.d + t.nt * kWideBN, p.d, valid,           \
+                           [&](int ml) { return p.row_w[row0 + ml]; }, acc, smem);             \
+    else                                                                                       \
+      wide_store<GATE_UP, DBL_>(p, t, row0, valid, acc);                                       \
+  } while (0)
 #define EXF_W_MAIN(DBL_, TMV_) wide_tile_mma<GATE_UP, DBL_, TMV_>(p, t, row0, valid, k0, k1, smem, acc)
   // the 32-row blocks 64 i + 32 wm of 128 rows, `rows` of which hold rows of the group
   auto live = [&](int rows) { return max(0, min(2, (rows - 32 * (wave >> 2) + 63) >> 6)); };
@@ -873,12 +872,7 @@ __device__ __forceinline__ void wide_gemm(const GemmKArgs &p, int G, bf16_t *sme
       case 1: EXF_W_MAIN(true, 1); break;
       default: EXF_W_MAIN(true, 0); break;
     }
-    if (part)
-      wide_store_partial<true>(part, acc);
-    else if (!GATE_UP && !DIRECT && p.Yh)
-      wide_store_lds<GATE_UP, DIRECT, NW, true>(p, t, row0, valid, acc, smem);
-    else
-      wide_store<GATE_UP, DIRECT, true>(p, t, row0, valid, acc);
+    EXF_W_STORE(true);
   } else {
     const int valid = min(kWide, p.offsets[t.g + 1] - row0);  // more than 128
     switch (2 + live(valid - 128)) {
@@ -886,14 +880,10 @@ __device__ __forceinline__ void wide_gemm(const GemmKArgs &p, int G, bf16_t *sme
       case 3: EXF_W_MAIN(false, 3); break;
       default: EXF_W_MAIN(false, 2); break;
     }
-    if (part)
-      wide_store_partial<false>(part, acc);
-    else if (!GATE_UP && !DIRECT && p.Yh)
-      wide_store_lds<GATE_UP, DIRECT, NW, false>(p, t, row0, valid, acc, smem);
-    else
-      wide_store<GATE_UP, DIRECT, false>(p, t, row0, valid, acc);
+    EXF_W_STORE(false);
   }
 #undef EXF_W_MAIN
+#undef EXF_W_STORE
 }
 
 
