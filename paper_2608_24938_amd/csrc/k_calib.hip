@@ -160,10 +160,11 @@ hipError_t launch_calib_gram(const float *Y, const int32_t *slot_row, int m, int
 // tile b of the permutation's tile list.  Thread (g, t) owns target t and the
 // g-th run of the tile's rows; the runs are added in order through LDS.  The
 // self pair (s, s) carries sum w and the row count (the norms).  Bound by the
-// latency of two dependent batches of gathers.  One thread a pair, and one an
+// gathers of two products a pair; the rows' own entries are loaded once a tile.  One thread a pair, and one an
 // expert for the norms, walking every token was a chain of m dependent loads:
-// 4096 tokens, top-8 of 128 experts took 1434 + 1361 us, now 33 + 5 us.
-constexpr int kPairThreads = 1024, kPairBatch = 8;
+// 4096 tokens, top-8 of 128 experts took 1434 + 1361 us, now 16 + 5 us (30 with
+// the rows' own entries loaded by every thread).
+constexpr int kPairThreads = 1024, kPairBatch = 8, kPairRows = 128;
 
 __global__ __launch_bounds__(kPairThreads) void calib_pairs_kernel(
     const double *__restrict__ gram, const int16_t *__restrict__ pos, const int32_t *__restrict__ offsets,
@@ -171,6 +172,8 @@ __global__ __launch_bounds__(kPairThreads) void calib_pairs_kernel(
     const int32_t *__restrict__ row_slot, int bm, int N, int NP, int kr, double *__restrict__ part) {
   __shared__ double red[3][kPairThreads];
   __shared__ int redn[kPairThreads];
+  __shared__ int tok[kPairRows], self[kPairRows];          // the rows' tokens and positions of s
+  __shared__ double norm[kPairRows], square[kPairRows];    // ||u_s|| and its square
   const int b = blockIdx.x;
   if (b >= tile_start[N]) return;
   __shared__ int src;  // the source whose tiles hold b (one round trip: every thread tests one)
@@ -178,45 +181,45 @@ __global__ __launch_bounds__(kPairThreads) void calib_pairs_kernel(
   __syncthreads();
   const int s = src;
   const int r0 = offsets[s] + (b - tile_start[s]) * bm, r1 = min(r0 + bm, offsets[s + 1]);
+  const int rows = r1 - r0;  // at most bm <= kPairRows
+  if ((int)threadIdx.x < rows) {
+    const int i = row_token[r0 + threadIdx.x], a = row_slot[r0 + threadIdx.x] - i * kr;
+    const double uu = gram[((long long)i * kr + a) * kr + a];
+    tok[threadIdx.x] = i;
+    self[threadIdx.x] = a;
+    square[threadIdx.x] = uu;
+    norm[threadIdx.x] = sqrt(uu);
+  }
+  __syncthreads();
   const int G = kPairThreads / NP, g = threadIdx.x / NP, t = threadIdx.x % NP;
-  const int per = (r1 - r0 + G - 1) / G;
-  const int q0 = r0 + g * per, q1 = min(q0 + per, r1);
+  const int per = (rows + G - 1) / G;
+  const int q0 = g * per, q1 = min(q0 + per, rows);
   double A = 0.0, V = 0.0, C = 0.0;
   int n = 0;
   if (t < N)
     for (int q = q0; q < q1; q += kPairBatch) {
       // loads of a batch of rows issued together: positions, then the products
       int pb[kPairBatch];
-      const double *Gi[kPairBatch];
-      double uu[kPairBatch], uv[kPairBatch], vv[kPairBatch];
-      int pa[kPairBatch];
+      double uv[kPairBatch], vv[kPairBatch];
 #pragma unroll
-      for (int u = 0; u < kPairBatch; ++u) {
-        pb[u] = -1;
-        if (q + u < q1) {
-          const int i = row_token[q + u];
-          pa[u] = row_slot[q + u] - i * kr;
-          pb[u] = pos[(long long)i * N + t];
-          Gi[u] = gram + (long long)i * kr * kr;
-        }
-      }
+      for (int u = 0; u < kPairBatch; ++u) pb[u] = q + u < q1 ? pos[(long long)tok[q + u] * N + t] : -1;
 #pragma unroll
       for (int u = 0; u < kPairBatch; ++u)
         if (pb[u] >= 0) {
-          uu[u] = Gi[u][pa[u] * kr + pa[u]];
-          uv[u] = Gi[u][pa[u] * kr + pb[u]];
-          vv[u] = Gi[u][pb[u] * kr + pb[u]];
+          const double *Gi = gram + (long long)tok[q + u] * kr * kr;
+          uv[u] = Gi[self[q + u] * kr + pb[u]];
+          vv[u] = Gi[pb[u] * kr + pb[u]];
         }
 #pragma unroll
       for (int u = 0; u < kPairBatch; ++u)
         if (pb[u] >= 0) {
-          const double w = sqrt(uu[u]);
+          const double w = norm[q + u];
           if (t == s) {
             A += w;
           } else {
             A += w * uv[u];
             V += w * vv[u];
-            C += w * uu[u];
+            C += w * square[q + u];
           }
           ++n;
         }

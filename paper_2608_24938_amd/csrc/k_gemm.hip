@@ -1351,11 +1351,12 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   // range keeps at least kMinSplitStages stages (an intermediate size of 768
   // split three ways ran 3 us slower per decode layer than unsplit, a 14336
   // one split in two 20 us faster).
-  const int bm = dn_skinny ? sk_m : tile_m;
+  // The split counts tiles of 32 (skinny) or 128 rows, whatever the tile height.
+  const int bm = dn_skinny ? sk_m : tile_m, split_m = dn_skinny ? 32 : 128;
   const int bn = dn_skinny ? kSkN : 128;
   const int kk = dn_skinny && inter % 128 == 0 ? 128 : kBK, fill = dn_skinny ? 3 : 2;
   *dn = GemmPlan{bm, bn, 1, 0, dn_skinny ? kGemmSkinny : kGemmTile};
-  const int mt_expect = (rows + bm - 1) / bm > active ? (rows + bm - 1) / bm : active;
+  const int mt_expect = (rows + split_m - 1) / split_m > active ? (rows + split_m - 1) / split_m : active;
   const int dn_tiles = mt_expect * (d / bn);
   constexpr int kMinSplitStages = 8;
   const int max_split = (inter / kk) / kMinSplitStages;
