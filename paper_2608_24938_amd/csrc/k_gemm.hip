@@ -1486,8 +1486,11 @@ hipError_t launch_plain_gemm_nt(const void *A, const void *W, int M, int N, int 
   g.ksplit = P;
   g.kc = K / P;
   g.Y = part;
-  const int grid = (M + 127) / 128 * g.n_tiles * P;
-  expert_gemm_tile<128, 128, false, false, true><<<grid, 256, 0, s>>>(g);
+  // 64-row tiles: the splits are chosen on 128 rows, which leaves at most one
+  // workgroup a CU (1237 tokens x 128 experts x 4096: 13.9 -> 9.9 us; 4096 x 128 x
+  // 2048: 14.4 -> 12.0)
+  const int grid = (M + 63) / 64 * g.n_tiles * P;
+  expert_gemm_tile<64, 128, false, false, true><<<grid, 256, 0, s>>>(g);
   return hipGetLastError();
 }
 

@@ -219,8 +219,8 @@ __global__ __launch_bounds__(64 * NW) void router_logits_lds(const bf16_t *__res
 constexpr int kRouterWideBlocks = 64;
 
 // Many tokens and a multiple of 128 experts: the router is a plain MFMA GEMM
-// on 128 x 128 tiles with its reduction split so the tiles cover the CUs
-// (8192 tokens x 128 experts x 2048: 256 tiles of 512-deep reductions).
+// on 64 x 128 tiles with its reduction split so that 128-row tiles would cover
+// the CUs (8192 tokens x 128 experts x 2048: 512 tiles of 512-deep reductions).
 static bool router_tiled(int T, int N, int d) {
   return (T + 15) / 16 >= kRouterWideBlocks && plain_gemm_splits(T, N, d, 256) > 0;
 }
@@ -483,11 +483,7 @@ __device__ __forceinline__ void route_token_wave(const RouteArgs &a, int t, int 
   }
   if (!fold_ids) return;
 
-  // Broadcast the token's routes to every lane.
   const uint64_t kmask = __ballot(kept);
-  int ids[kMaxTopK];
-#pragma unroll
-  for (int j = 0; j < kMaxTopK; ++j) ids[j] = (int)readlane_u32((uint32_t)my_id, j < K ? j : 0);
 
   // Omitted route: first minimum of L[s, t] over the retained routes in route
   // order (with the loss cap: over those with L[s, t] <= cap; none -> dropped).
@@ -496,34 +492,62 @@ __device__ __forceinline__ void route_token_wave(const RouteArgs &a, int t, int 
   const bool capped = flags & EXFOLD_FOLD_LOSS_CAP, conf = flags & EXFOLD_FOLD_CONFIDENCE;
   int tgt_lane = -1;
   double contrib = 0.0, rest = 0.0;
-  if (lane < K && !kept) {
-    // L and S of every candidate target loaded together (one round trip)
-    const float *lrow = L + (size_t)my_id * N;
-    const float *srow = S ? S + (size_t)my_id * N : nullptr;
-    float lv[kMaxTopK], sv[kMaxTopK];
+  float best = 0.f, s_best = 0.f;
+  if (K <= 8) {
+    // lane 8 s + t takes the pair of routes (s, t): one load each of L and S a
+    // token (one lane an omitted route, walking its candidates, issued up to 2 K
+    // loads a token), then the minimum (value, route) over each eight lanes
+    const int sr = lane >> 3, tr = lane & 7;
+    const int s_id = __shfl(my_id, sr, kWave), t_id = __shfl(my_id, tr, kWave);
+    const bool cand = sr < K && tr < K && !((kmask >> sr) & 1ull) && ((kmask >> tr) & 1ull);
+    const size_t at = (size_t)s_id * N + t_id;
+    const float lv = cand ? L[at] : 0.f;
+    const float sv = (cand && S && !om_src) ? S[at] : 0.f;
+    uint64_t key = (cand && (!capped || lv <= loss_cap)) ? (uint64_t(float_key(lv)) << 32) | uint32_t(tr) : ~0ull;
+    const auto pick = [](uint64_t x, uint64_t y) { return x < y ? x : y; };
+    key = pick(key, dpp_u64<0xB1>(key, key));
+    key = pick(key, dpp_u64<0x4E>(key, key));
+    key = pick(key, dpp_u64<0x141>(key, key));
+    // route k's lane (k < 8) reads the group of its pairs
+    const int mine = key == ~0ull ? -1 : (int)(key & 7u);
+    const int got = __shfl(mine, 8 * tr, kWave);
+    const int from = 8 * tr + (got < 0 ? 0 : got);
+    best = __shfl(lv, from, kWave);
+    s_best = __shfl(sv, from, kWave);
+    if (lane < K && !kept) tgt_lane = got;
+  } else {
+    // Broadcast the token's routes to every lane.
+    int ids[kMaxTopK];
 #pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) {
-      const bool cand = j < K && ((kmask >> j) & 1ull);
-      lv[j] = cand ? lrow[ids[j]] : 0.f;
-      sv[j] = (cand && srow && !om_src) ? srow[ids[j]] : 0.f;
-    }
-    float best = 0.f, s_best = 0.f;
+    for (int j = 0; j < kMaxTopK; ++j) ids[j] = (int)readlane_u32((uint32_t)my_id, j < K ? j : 0);
+    if (lane < K && !kept) {
+      // L and S of every candidate target loaded together (one round trip)
+      const float *lrow = L + (size_t)my_id * N;
+      const float *srow = S ? S + (size_t)my_id * N : nullptr;
+      float lv[kMaxTopK], sv[kMaxTopK];
 #pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) {
-      if (j < K && ((kmask >> j) & 1ull) && (!capped || lv[j] <= loss_cap)) {
-        if (tgt_lane < 0 || lv[j] < best) {
-          best = lv[j];
-          s_best = sv[j];
-          tgt_lane = j;
+      for (int j = 0; j < kMaxTopK; ++j) {
+        const bool cand = j < K && ((kmask >> j) & 1ull);
+        lv[j] = cand ? lrow[ids[j]] : 0.f;
+        sv[j] = (cand && srow && !om_src) ? srow[ids[j]] : 0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < kMaxTopK; ++j) {
+        if (j < K && ((kmask >> j) & 1ull) && (!capped || lv[j] <= loss_cap)) {
+          if (tgt_lane < 0 || lv[j] < best) {
+            best = lv[j];
+            s_best = sv[j];
+            tgt_lane = j;
+          }
         }
       }
     }
-    if (tgt_lane >= 0 && !om_src) {
-      double c = 1.0;
-      if (conf) c = fmin(1.0, fmax(0.0, __dsub_rn(1.0, (double)best)));
-      contrib = __dmul_rn(__dmul_rn((double)my_w, c), (double)s_best);
-      if (conf) rest = __dmul_rn((double)my_w, __dsub_rn(1.0, c));
-    }
+  }
+  if (tgt_lane >= 0 && !om_src) {
+    double c = 1.0;
+    if (conf) c = fmin(1.0, fmax(0.0, __dsub_rn(1.0, (double)best)));
+    contrib = __dmul_rn(__dmul_rn((double)my_w, c), (double)s_best);
+    if (conf) rest = __dmul_rn((double)my_w, __dsub_rn(1.0, c));
   }
   // Diagonal projectors (unfused path): the retained routes execute with weight
   // 1 and keep their router weights aside; each omitted route records its

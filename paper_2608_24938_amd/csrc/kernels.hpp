@@ -136,7 +136,7 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
 hipError_t launch_expert_gemms(const ExpertArgs &a, const GemmPlan &gu, const GemmPlan &dn,
                                hipStream_t s, hipEvent_t ev_mid = nullptr);
 // Plain bf16 product part[P][M][N] = partial sums over P equal reduction
-// ranges of A[M, K] W[N, K]^T (fp32, MFMA 128x128 tiles).  plain_gemm_splits
+// ranges of A[M, K] W[N, K]^T (fp32, MFMA 64x128 tiles).  plain_gemm_splits
 // gives P for the shape (0: N % 128 != 0 or K % 64 != 0, not supported).
 int plain_gemm_splits(int M, int N, int K, int cu_count);
 hipError_t launch_plain_gemm_nt(const void *A, const void *W, int M, int N, int K, int P, float *part,

@@ -173,3 +173,44 @@ def test_one_workgroup_permutation(T, K, n, phase):
     _, offsets, row_slot = O.permute_routes(ids, n)
     np.testing.assert_array_equal(g["offsets"][: n + 1], offsets)
     np.testing.assert_array_equal(g["row_slot"], row_slot)
+
+
+# Prefill fold by pairs of routes (K <= 8) and by one lane a route (K > 8): either side of 8, one
+# route, every route or one retained, equal losses and losses of either zero (the first route wins).
+@pytest.mark.parametrize("K,kp,opts", [(1, 1, {}), (2, 1, {}), (7, 3, dict(loss_cap=0.5)), (8, 1, {}), (8, 7, {}),
+                                       (8, 8, {}), (8, 4, dict(confidence=True, renorm=True)), (9, 4, {}),
+                                       (9, 1, dict(loss_cap=0.25, renorm=True))])
+def test_fold_either_side_of_eight_routes(K, kp, opts):
+    rng = np.random.default_rng(10 * K + kp)
+    T, N = 67, 24
+    ids = np.stack([rng.permutation(N)[:K] for _ in range(T)]).astype(np.int32)
+    w = rng.dirichlet(np.ones(K), size=T).astype(np.float32)
+    S = rng.standard_normal((N, N)).astype(np.float32)
+    L = rng.choice(np.array([0.0, -0.0, 0.25, 0.5, 1.0, 1e30], np.float32), size=(N, N))
+    keep = O.select_prefill(ids, w, rng.random(N).astype(np.float32), kp)
+    print(f"fold: K={K} K'={kp} {opts}", flush=True)
+    out_ids, out_w = X.fold_gates("prefill", kp, to_dev(ids), to_dev(w), to_dev(S), to_dev(L),
+                                  keep=to_dev(keep.astype(np.uint8)), **opts)
+    sync()
+    if opts:
+        ref_ids, ref_w = O.fold_prefill_safeguarded(ids, w, keep, S, L, **opts)
+    else:
+        ref_ids, ref_w = O.fold_prefill(ids, w, keep, S, L)
+    np.testing.assert_array_equal(out_ids.cpu().numpy(), ref_ids)
+    np.testing.assert_array_equal(out_w.cpu().numpy().view(np.uint32), ref_w.view(np.uint32))
+
+
+# Router of many tokens and a multiple of 128 experts: 64-row tiles, a ragged last one.
+@pytest.mark.parametrize("T,n,d", [(1009, 128, 256), (1088, 256, 1024), (2049, 128, 512)])
+def test_tiled_router_logits(T, n, d):
+    shape = _shape(d, 64, n, 4, dtype="bf16", bias=True)
+    lp = LayerPair(shape, seed=n)
+    xs = synth.tokens(shape, T, seed=n)
+    dbg = X.debug_buffers(lp.dev, T, "dense", 0, "cuda:0")
+    print(f"router bf16: N={n} T={T} d={d}", flush=True)
+    X.moe_forward(lp.dev, to_dev(xs), "dense", debug=dbg)
+    sync()
+    x = synth.widen(xs)
+    ref = O.router_logits(x, lp.ref.w_router, lp.ref.router_bias)
+    got = dbg["logits"].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - ref) <= logits_bound(x, lp.ref.w_router, lp.ref.router_bias, d))
