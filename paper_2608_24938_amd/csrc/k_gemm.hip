@@ -48,8 +48,9 @@ __device__ __forceinline__ float silu(float g) { return g * __builtin_amdgcn_rcp
 
 constexpr int kBK = 64;
 
-// 16 bytes of a weight row; ONCE: no other tile reads it (TileId::alone), and the
-// load is non-temporal.  Such streams neither evict the rows, tables and
+// 16 bytes of a weight row; ONCE: no other tile reads it (TileId::alone; skinny
+// tiles always, whose groups seldom take a second m-tile: two builds of their main
+// loop cost 2-3% more than the hint does there), and the load is non-temporal.  Such streams neither evict the rows, tables and
 // activations that are read again nor wait for the room: Mixtral-shaped
 // decode gate/up 163 -> 149 us, down 85 -> 77, GLM-shaped (64 tokens, pool of 32)
 // 141 -> 129 and 79 -> 71.  Where several m-tiles share a weight row the hint costs
