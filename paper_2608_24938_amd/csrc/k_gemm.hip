@@ -429,11 +429,16 @@ constexpr int kWideSmemElems = 2 * (kWide / 2 + 2 * kWideBN) * kWideBK;
 //
 // Half tiles are issued in the order they are read.  Full tiles: numbered so,
 // phase p reads tile p + 1 and issues tile p + 7 (two loads a wave) into the slot
-// that phase p - 2 read: the later waves' MFMAs of phase p - 2, and so their
-// reads, ended at a barrier before this phase began.  Before the phase's
-// barrier tile p + 2 must have landed: at most five tiles, 10 loads, stay in
-// flight; a load has six phases (1.5 stages) to land.  Tail tiles: five tiles a
-// stage on four phases (the second issues two), six or seven stay in flight.
+// that phase p - 2 read: the later waves met the barrier that ends their phase
+// p - 2 before this phase began, and every wave waits for all its LDS reads
+// before that barrier.  (The MFMAs alone do not order them: those of a stage's
+// last phase do not use the weight half that it reads for the next stage, and
+// no MFMA precedes the first phase.  The reads are a block of MFMAs old by then,
+// so the wait costs nothing: Qwen3-shaped prefill 461 us a layer without it, 464
+// with it, on two boxes.)  Before the phase's barrier tile p + 2 must have landed:
+// at most five tiles, 10 loads, stay in flight; a load has six phases (1.5
+// stages) to land.  Tail tiles: five tiles a stage on four phases (the second
+// issues two), six or seven stay in flight.
 //
 // One barrier a stage with every wave reading, loading and multiplying at once
 // (one stage ahead) kept the MFMA pipes busy 57% of the cycles, this 72% of them
@@ -517,6 +522,8 @@ __device__ __forceinline__ void wide_tile_mma(const GemmKArgs &p, const TileId &
           *reinterpret_cast<const bf16x8 *>(fb_at[s_] + (2 * (G_) + (BUF_)) * HALF);    \
   } while (0)
 #define EXF_P_BARRIER() asm volatile("s_barrier" ::: "memory")
+  // the end of a phase: the wave's LDS reads have ended, then the barrier
+#define EXF_P_CLOSE() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
   // products of row half H_ (full tiles) or weight pair H_ (tail tiles) with weight half J_ of it
 #define EXF_P_MMA(H_, J_)                                                               \
   do {                                                                                  \
@@ -528,7 +535,7 @@ __device__ __forceinline__ void wide_tile_mma(const GemmKArgs &p, const TileId &
                 fb[J_][s_], fa[i_][s_], acc[2 * (H_) + i_][J_], 0, 0, 0);               \
     __builtin_amdgcn_s_setprio(0);                                                      \
     __builtin_amdgcn_sched_barrier(0);                                                  \
-    EXF_P_BARRIER();                                                                    \
+    EXF_P_CLOSE();                                                                      \
   } while (0)
   // at most VM_ of the wave's loads are in flight, then the barrier
 #define EXF_P_WAIT(VM_) asm volatile("s_waitcnt vmcnt(" #VM_ ")\n\ts_barrier" ::: "memory")
@@ -608,7 +615,7 @@ __device__ __forceinline__ void wide_tile_mma(const GemmKArgs &p, const TileId &
     EXF_P_BEGIN(1);
   else
     EXF_P_BEGIN(0);
-  if (wave >= 4) EXF_P_BARRIER();  // half a phase behind
+  if (wave >= 4) EXF_P_CLOSE();  // half a phase behind; the first weight half has been read
   if constexpr (DBL) {
     if (odd) {
       EXF_P_TAIL(1, true, true, 12, 14, 12, 12, true);
@@ -640,6 +647,7 @@ __device__ __forceinline__ void wide_tile_mma(const GemmKArgs &p, const TileId &
 #undef EXF_P_READ_A
 #undef EXF_P_READ_B
 #undef EXF_P_BARRIER
+#undef EXF_P_CLOSE
 #undef EXF_P_MMA
 #undef EXF_P_WAIT
 #undef EXF_P_STAGE
