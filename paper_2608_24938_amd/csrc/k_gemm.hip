@@ -1360,13 +1360,19 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   // range keeps at least kMinSplitStages stages (an intermediate size of 768
   // split three ways ran 3 us slower per decode layer than unsplit, a 14336
   // one split in two 20 us faster).
-  // The split counts tiles of 32 (skinny) or 128 rows, whatever the tile height.
-  const int bm = dn_skinny ? sk_m : tile_m, split_m = dn_skinny ? 32 : 128;
+  // The split is counted on 32 x 64 tiles, three a CU, where skinny tiles take an
+  // even multiple of 64 columns, and on 128 x 128 tiles, two a CU, otherwise,
+  // whatever the tile that runs: with one range the rows travel as bf16, with more
+  // as float32 partials, so a count on the smaller tiles, which asks for fewer
+  // ranges, would take precision from odd multiples of 64 (d 512, I 1728, 1598 rows
+  // on 34 experts: three ranges).
+  const int bm = dn_skinny ? sk_m : tile_m;
   const int bn = dn_skinny ? kSkN : 128;
-  const int kk = dn_skinny && inter % 128 == 0 ? 128 : kBK, fill = dn_skinny ? 3 : 2;
+  const bool fine = dn_skinny && inter % 128 == 0;
+  const int split_m = fine ? 32 : 128, split_n = fine ? kSkN : 128, kk = fine ? kSkK : kBK, fill = fine ? 3 : 2;
   *dn = GemmPlan{bm, bn, 1, 0, dn_skinny ? kGemmSkinny : kGemmTile};
   const int mt_expect = (rows + split_m - 1) / split_m > active ? (rows + split_m - 1) / split_m : active;
-  const int dn_tiles = mt_expect * (d / bn);
+  const int dn_tiles = mt_expect * (d / split_n);
   constexpr int kMinSplitStages = 8;
   const int max_split = (inter / kk) / kMinSplitStages;
   if (dn_tiles < fill * cu_count && max_split >= 2) {

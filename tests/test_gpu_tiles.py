@@ -124,13 +124,14 @@ def test_wide_tile_edges(d, inter, k):
 # Skinny tiles of 32 and 64 rows (up to 12 and up to 24 gate/up or 48 down rows per busy expert) and
 # 64-row down tiles (up to 80): groups of 0, 1, 32, 33, 64, 65 and more rows; reductions that end
 # in half a 128-column stage (I = 192, 320, 704), of one stage (I = 128) and below one (I = 64); one and
-# several routes a token, the shared expert, a split down reduction (I = 4096, few tiles).
+# several routes a token, the shared expert, a split down reduction (I = 4096; I = 1728 and 4160: ranges that end in half a stage).
 @pytest.mark.parametrize("d,inter,sizes,k,shared", [
     (256, 192, [1, 0, 32, 33, 0, 2, 4, 0], 1, 0), (256, 192, [1, 0, 12, 33, 0, 24, 9, 1], 2, 192),
     (128, 320, [64, 65, 0, 32, 33, 1, 3, 2], 1, 0), (384, 704, [64, 65, 0, 32, 33, 1, 3, 2], 2, 0),
     (128, 128, [40, 30, 20, 60], 2, 128), (256, 64, [20, 10, 5, 1], 1, 0), (256, 64, [20, 10, 5, 1], 2, 0),
     (256, 320, [64, 65, 63, 128, 129, 1], 2, 0), (640, 192, [64, 65, 63, 128, 20, 1], 1, 0),
     (128, 4096, [3, 1, 0, 4], 2, 0), (128, 4160, [40, 50, 33, 65], 2, 0),
+    (512, 1728, [47] * 34, 2, 0),
     # more than two 128-column down tiles a CU: 64-row tiles from 21 rows on average, skinny at 20
     (2048, 128, [21] * 33, 1, 0), (2048, 192, [20] * 33, 1, 0), (4096, 64, [64, 1, 0, 65, 33] * 7, 2, 0)])
 def test_streaming_tile_edges(d, inter, sizes, k, shared):

@@ -51,6 +51,19 @@ def test_kernel_family(shape, rows, active, gu_kind, dn_kind):
     assert (gu["kind"], dn["kind"]) == (gu_kind, dn_kind), (gu, dn)
 
 
+# One range: the rows travel as bf16.  More: as float32 partials.  An intermediate size that is an odd multiple
+# of 64 is split as its count of 128 x 128 tiles asks for, on whatever tiles it runs.
+@pytest.mark.parametrize("d,inter,n,active,rows,ksplit", [
+    (512, 1728, 64, 34, 1598, 3), (7168, 4160, 8, 2, 16, 5), (7168, 14400, 8, 4, 16, 3), (640, 6720, 65, 13, 319, 7),
+    (512, 4800, 49, 28, 80, 5), (4480, 4928, 2, 1, 1, 7), (640, 960, 8, 1, 4, 1),
+    (7168, 4096, 8, 2, 16, 4), (4096, 14336, 8, 4, 64, 2),   # even multiples: three 32 x 64 tiles a CU
+])
+def test_down_split(d, inter, n, active, rows, ksplit):
+    _, dn = plan(layer(d, inter, n, 1), rows, active)
+    assert dn["ksplit"] == ksplit, dn
+    assert inter // 64 % ksplit == 0
+
+
 def test_float32_layers_take_the_simt_kernels():
     gu, dn = plan(layer(256, 512, 8, 2, dtype=X.F32), 64, 8)
     assert gu["kind"] == dn["kind"] == SIMT
