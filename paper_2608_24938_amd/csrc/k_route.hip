@@ -503,7 +503,10 @@ __device__ __forceinline__ void route_token_wave(const RouteArgs &a, int t, int 
     const size_t at = (size_t)s_id * N + t_id;
     const float lv = cand ? L[at] : 0.f;
     const float sv = (cand && S && !om_src) ? S[at] : 0.f;
-    uint64_t key = (cand && (!capped || lv <= loss_cap)) ? (uint64_t(float_key(lv)) << 32) | uint32_t(tr) : ~0ull;
+    // keys order as strict `<` scans: a NaN stays where it is the first candidate
+    // (key 0) and is passed over anywhere else (above every loss)
+    const uint32_t order = lv == lv ? float_key(lv) : (kmask & lanemask_lt(tr)) == 0ull ? 0u : ~0u;
+    uint64_t key = (cand && (!capped || lv <= loss_cap)) ? (uint64_t(order) << 32) | uint32_t(tr) : ~0ull;
     const auto pick = [](uint64_t x, uint64_t y) { return x < y ? x : y; };
     key = pick(key, dpp_u64<0xB1>(key, key));
     key = pick(key, dpp_u64<0x4E>(key, key));

@@ -201,6 +201,31 @@ def test_fold_either_side_of_eight_routes(K, kp, opts):
     np.testing.assert_array_equal(out_w.cpu().numpy().view(np.uint32), ref_w.view(np.uint32))
 
 
+# The first minimum under strict `<`, as the oracle scans: a NaN loss (of either sign) is taken only as the
+# first candidate and loses to nothing then, is never within a cap, and an infinite loss is an ordinary value.
+@pytest.mark.parametrize("K,kp", [(2, 1), (3, 2), (8, 1), (8, 3), (8, 7), (9, 3), (16, 5)])
+@pytest.mark.parametrize("opts", [{}, dict(loss_cap=0.5), dict(loss_cap=float("inf"), renorm=True)])
+def test_fold_of_nan_and_infinite_losses(K, kp, opts):
+    rng = np.random.default_rng(100 * K + kp)
+    T, N = 131, 24
+    ids = np.stack([rng.permutation(N)[:K] for _ in range(T)]).astype(np.int32)
+    w = rng.dirichlet(np.ones(K), size=T).astype(np.float32)
+    S = rng.standard_normal((N, N)).astype(np.float32)
+    nan = np.float32("nan")
+    L = rng.choice(np.array([nan, -nan, nan, np.inf, -np.inf, -0.0, 0.25, 0.5, 1.0], np.float32), size=(N, N))
+    keep = O.select_prefill(ids, w, rng.random(N).astype(np.float32), kp)
+    print(f"fold with NaN: K={K} K'={kp} {opts}", flush=True)
+    out_ids, out_w = X.fold_gates("prefill", kp, to_dev(ids), to_dev(w), to_dev(S), to_dev(L),
+                                  keep=to_dev(keep.astype(np.uint8)), **opts)
+    sync()
+    if opts:
+        ref_ids, ref_w = O.fold_prefill_safeguarded(ids, w, keep, S, L, **opts)
+    else:
+        ref_ids, ref_w = O.fold_prefill(ids, w, keep, S, L)
+    np.testing.assert_array_equal(out_ids.cpu().numpy(), ref_ids)
+    np.testing.assert_array_equal(out_w.cpu().numpy().view(np.uint32), ref_w.view(np.uint32))
+
+
 # Router of many tokens and a multiple of 128 experts: 64-row tiles, a ragged last one.
 @pytest.mark.parametrize("T,n,d", [(1009, 128, 256), (1088, 256, 1024), (2049, 128, 512)])
 def test_tiled_router_logits(T, n, d):
