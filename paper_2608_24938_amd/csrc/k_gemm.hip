@@ -48,20 +48,35 @@ __device__ __forceinline__ float silu(float g) { return g * __builtin_amdgcn_rcp
 
 constexpr int kBK = 64;
 
-// 16 bytes of a weight row; ONCE: no other tile reads it (TileId::alone; skinny
-// tiles always, whose groups seldom take a second m-tile: two builds of their main
-// loop cost 2-3% more than the hint does there), and the load is non-temporal.  Such streams neither evict the rows, tables and
-// activations that are read again nor wait for the room: Mixtral-shaped
-// decode gate/up 163 -> 149 us, down 85 -> 77, GLM-shaped (64 tokens, pool of 32)
-// 141 -> 129 and 79 -> 71.  Where several m-tiles share a weight row the hint costs
-// more than it gives (64-row down tiles of 512 Qwen3-shaped tokens, pool of 64,
-// 55 -> 68; every wide tile 5%).
+// 16 bytes of a weight row; ONCE: no other tile reads it (TileId::alone), and the
+// load is non-temporal.  Such streams neither evict the rows, tables and activations
+// that are read again nor wait for the room: Mixtral-shaped decode gate/up 163 ->
+// 149 us, down 85 -> 77, GLM-shaped (64 tokens, pool of 32) 141 -> 129 and 79 -> 71.
+// Where several m-tiles share a weight row the hint costs more than it gives (64-row
+// down tiles of 512 Qwen3-shaped tokens, pool of 64, 55 -> 68 us; every wide tile
+// 5%; 256 tokens on 128 Qwen3-shaped experts, some with up to 175 rows, the layer:
+// no hint 256, on every weight row 266, on single m-tiles 235).  It loses only where
+// the weights fit the last-level cache and nothing else runs between two calls (32
+// experts, d 1024, I 512, 300 tokens x 4, skewed: 46.1 -> 48.2 us; with 2 GB of other
+// layers between them 50.8 -> 48.3).
 template <bool ONCE>
 __device__ __forceinline__ u32x4 load_w16(const bf16_t *p) {
   if constexpr (ONCE)
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
   else
     return *reinterpret_cast<const u32x4 *>(p);
+}
+
+// Start of a main loop whose weight loads are load_w16<ONCE>, in a kernel that holds
+// one of each.  An instruction that the two loops do not have in common: the compiler
+// otherwise hoists the first loads out of both as plain ones and waits for all of
+// them at the loop head (2-3% of a skinny launch).
+template <bool ONCE>
+__device__ __forceinline__ void mark_loads() {
+  if constexpr (ONCE)
+    asm volatile("; weights read once");
+  else
+    asm volatile("; weights shared");
 }
 
 // LDS element offset of 16-byte chunk q of tile row r (8 chunks per 128-byte row).
@@ -1039,7 +1054,7 @@ __global__ __launch_bounds__(256, RB == 1 ? 3 : 2) void expert_gemm_skinny(const
     const int k_ = min((KT_) * kSkK, k_last);                                               \
     _Pragma("unroll") for (int i_ = 0; i_ < PA; ++i_) RA_[i_] =                             \
         *reinterpret_cast<const u32x4 *>(a_src[i_] + k_);                                   \
-    _Pragma("unroll") for (int i_ = 0; i_ < PB; ++i_) RB_[i_] = load_w16<true>(b_src[i_] + k_); \
+    _Pragma("unroll") for (int i_ = 0; i_ < PB; ++i_) RB_[i_] = load_w16<ONCE>(b_src[i_] + k_); \
   } while (0)
 #define EXF_SK_LSTORE(RA, RB, BUF)                                                          \
   do {                                                                                      \
@@ -1080,23 +1095,31 @@ __global__ __launch_bounds__(256, RB == 1 ? 3 : 2) void expert_gemm_skinny(const
   // new, the k16 steps of its lower half are not taken again.
   const int KT = (p.kc + kSkK - 1) / kSkK, k_last = p.kc - kSkK;
   const bool half = (p.kc & (kSkK - 1)) != 0;
-  u32x4 ra0[PA], rb0[PB], ra1[PA], rb1[PB];
-  EXF_SK_GLOAD(ra0, rb0, 0);
-  EXF_SK_LSTORE(ra0, rb0, 0);
-  EXF_SK_GLOAD(ra1, rb1, 1);
-  __syncthreads();
-  int kt = 0;
-  for (; kt + 2 <= KT; kt += 2) {
-    EXF_SK_GLOAD(ra0, rb0, kt + 2);
-    EXF_SK_COMPUTE(0, kt);
-    EXF_SK_LSTORE(ra1, rb1, 1);
-    __syncthreads();
-    EXF_SK_GLOAD(ra1, rb1, kt + 3);
-    EXF_SK_COMPUTE(1, kt + 1);
+  auto main_loop = [&](auto once) __attribute__((always_inline)) {
+    constexpr bool ONCE = decltype(once)::value;
+    mark_loads<ONCE>();
+    u32x4 ra0[PA], rb0[PB], ra1[PA], rb1[PB];
+    EXF_SK_GLOAD(ra0, rb0, 0);
     EXF_SK_LSTORE(ra0, rb0, 0);
+    EXF_SK_GLOAD(ra1, rb1, 1);
     __syncthreads();
-  }
-  if (kt < KT) EXF_SK_COMPUTE(0, kt);
+    int kt = 0;
+    for (; kt + 2 <= KT; kt += 2) {
+      EXF_SK_GLOAD(ra0, rb0, kt + 2);
+      EXF_SK_COMPUTE(0, kt);
+      EXF_SK_LSTORE(ra1, rb1, 1);
+      __syncthreads();
+      EXF_SK_GLOAD(ra1, rb1, kt + 3);
+      EXF_SK_COMPUTE(1, kt + 1);
+      EXF_SK_LSTORE(ra0, rb0, 0);
+      __syncthreads();
+    }
+    if (kt < KT) EXF_SK_COMPUTE(0, kt);
+  };
+  if (__builtin_amdgcn_readfirstlane(t.alone))
+    main_loop(std::true_type{});
+  else
+    main_loop(std::false_type{});
 #undef EXF_SK_GLOAD
 #undef EXF_SK_LSTORE
 #undef EXF_SK_COMPUTE
@@ -1312,7 +1335,14 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   // tiles a CU (Qwen3-shaped, one token: 54.9 against 56.4 us).  d is a multiple
   // of 128; a reduction shorter than one skinny stage (I = 64) takes the tile.
   const bool gu_skinny = rows <= 24 * active;
-  const int sk_m = rows <= 12 * active ? 32 : 64;
+  // 64-row skinny tiles only where there are more than four tiles a CU: two of
+  // them fit a CU and three of 32 rows, so a launch of few tiles takes a second
+  // round as soon as some experts hold more than 64 rows (32 experts, d 1024, I 512,
+  // 180 tokens x 4, one expert with 99 rows: 46.0 against 40.7 us a layer; with every
+  // expert below 34 rows 37.8 against 39.9).
+  const auto skinny_rows = [&](int tiles) {
+    return rows <= 12 * active || (rows <= 24 * active && tiles <= 4 * cu_count) ? 32 : 64;
+  };
   // Many rows per retained expert (prefill, at least 128 on average): wide
   // tiles.  With the 128-row tail tiles a skewed load pays at most half a tile
   // per group: the Qwen3-shaped prefill (8192 tokens, K' = 4, 98 of 128 experts
@@ -1334,6 +1364,7 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   const bool dn_skinny = inter >= kSkK && rows <= (active * (d / 128) > 2 * cu_count ? 20 : 48) * active;
   const int tile_m = rows <= 80 * active ? 64 : 128;
   if (gu_skinny) {
+    const int sk_m = skinny_rows(active * (inter / (kSkN / 2)));
     *gu = GemmPlan{sk_m, kSkN, 1, 0, kGemmSkinny};
     gu->grid = (rows / sk_m + groups) * (inter / (kSkN / 2));  // >= sum of ceil(rows_g / bm) tiles
   } else if (gu_wide) {
@@ -1366,11 +1397,10 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
   // as float32 partials, so a count on the smaller tiles, which asks for fewer
   // ranges, would take precision from odd multiples of 64 (d 512, I 1728, 1598 rows
   // on 34 experts: three ranges).
-  const int bm = dn_skinny ? sk_m : tile_m;
   const int bn = dn_skinny ? kSkN : 128;
   const bool fine = dn_skinny && inter % 128 == 0;
   const int split_m = fine ? 32 : 128, split_n = fine ? kSkN : 128, kk = fine ? kSkK : kBK, fill = fine ? 3 : 2;
-  *dn = GemmPlan{bm, bn, 1, 0, dn_skinny ? kGemmSkinny : kGemmTile};
+  *dn = GemmPlan{0, bn, 1, 0, dn_skinny ? kGemmSkinny : kGemmTile};
   const int mt_expect = (rows + split_m - 1) / split_m > active ? (rows + split_m - 1) / split_m : active;
   const int dn_tiles = mt_expect * (d / split_n);
   constexpr int kMinSplitStages = 8;
@@ -1380,7 +1410,8 @@ void plan_expert_gemms(int dtype, int rows, int groups, int active_groups, int d
     const int cap = want < max_split ? want : max_split;
     dn->ksplit = largest_divisor_at_most(inter / kk, cap > 8 ? 8 : cap);
   }
-  dn->grid = (rows / bm + groups) * (d / bn) * dn->ksplit;
+  dn->bm = dn_skinny ? skinny_rows(active * (d / kSkN) * dn->ksplit) : tile_m;
+  dn->grid = (rows / dn->bm + groups) * (d / bn) * dn->ksplit;
 }
 
 hipError_t launch_expert_gemms(const ExpertArgs &a, const GemmPlan &gu, const GemmPlan &dn,

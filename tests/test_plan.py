@@ -64,6 +64,18 @@ def test_down_split(d, inter, n, active, rows, ksplit):
     assert inter // 64 % ksplit == 0
 
 
+# Skinny tiles: 32 rows up to 12 rows a busy expert, and up to 24 where there are at most four tiles a CU; else 64.
+@pytest.mark.parametrize("shape,rows,active,gu_bm,dn_bm", [
+    (QWEN3, 12 * 64, 64, 32, 32), (QWEN3, 12 * 64 + 1, 64, 64, 64), (QWEN3, 12 * 128 + 1, 128, 64, 64),
+    (MIXTRAL, 96, 8, 32, 32), (MIXTRAL, 97, 8, 64, 32), (MIXTRAL, 24 * 8, 8, 64, 32), (MIXTRAL, 24 * 8 + 1, 8, 128, 64),
+    (dict(d=1024, inter=512, n=32, k=4), 720, 32, 32, 32), (dict(d=1024, inter=512, n=32, k=4), 769, 32, 128, 64),
+    (dict(d=2048, inter=768, n=32, k=4), 640, 32, 32, 32), (dict(d=2048, inter=1088, n=32, k=4), 640, 32, 64, 32),
+])
+def test_skinny_tile_height(shape, rows, active, gu_bm, dn_bm):
+    gu, dn = plan(layer(**shape), rows, active)
+    assert (gu["bm"], dn["bm"]) == (gu_bm, dn_bm), (gu, dn)
+
+
 def test_float32_layers_take_the_simt_kernels():
     gu, dn = plan(layer(256, 512, 8, 2, dtype=X.F32), 64, 8)
     assert gu["kind"] == dn["kind"] == SIMT
