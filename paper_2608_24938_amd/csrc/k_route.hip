@@ -1340,9 +1340,12 @@ __global__ __launch_bounds__(kPoolThreads) void decode_front_kernel(
       m &= set ? bal : ~bal;
     }
     const int before = __popcll(m & lanemask_lt(lane));
-    const int seen = wcnt[wave][te];  // of the wave's earlier steps (its own LDS accesses stay in order)
+    // seen by the wave's earlier steps, whose leading lanes may be other lanes
+    const int seen = wcnt[wave][te];
     rank[s] = seen + before;
+    wave_lds_order();
     if (valid && before == 0) wcnt[wave][te] = seen + __popcll(m);
+    wave_lds_order();
   }
   lds_barrier();
 
