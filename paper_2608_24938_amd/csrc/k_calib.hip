@@ -52,7 +52,8 @@ hipError_t launch_calib_routes(const int32_t *topk_ids, int m, int N, int K, int
   return hipGetLastError();
 }
 
-// Gram matrices on the float64 MFMA (16x16x4, exact float64 products and sums).
+// Gram matrices on the float64 MFMA (16x16x4; a product of two float32 values is
+// exact in float64, the sums are rounded, in one fixed order).
 // A tile's 16 rows are the rows of 16 / P tokens side by side (P: kr rounded up
 // to a power of two; kr > 16: one token, 16 x 16 tiles ta <= tb).  Lane l holds
 // eight consecutive columns of row l % 16 at 8 (l / 16), and MFMA step q takes
@@ -164,7 +165,8 @@ hipError_t launch_calib_gram(const float *Y, const int32_t *slot_row, int m, int
 // expert for the norms, walking every token was a chain of m dependent loads:
 // 4096 tokens, top-8 of 128 experts took 1434 + 1361 us, now 16 + 5 us (30 with
 // the rows' own entries loaded by every thread).
-constexpr int kPairThreads = 1024, kPairBatch = 8, kPairRows = 128;
+constexpr int kPairThreads = 1024, kPairBatch = 8;
+constexpr int kPairRows = 128;  // tallest tile of the GEMM planner (wide tiles are listed in 128-row units)
 
 __global__ __launch_bounds__(kPairThreads) void calib_pairs_kernel(
     const double *__restrict__ gram, const int16_t *__restrict__ pos, const int32_t *__restrict__ offsets,
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(kPairThreads) void calib_pairs_kernel(
   __syncthreads();
   const int s = src;
   const int r0 = offsets[s] + (b - tile_start[s]) * bm, r1 = min(r0 + bm, offsets[s + 1]);
-  const int rows = r1 - r0;  // at most bm <= kPairRows
+  const int rows = r1 - r0;  // at most bm <= kPairRows (launch_calib_finalize)
   if ((int)threadIdx.x < rows) {
     const int i = row_token[r0 + threadIdx.x], a = row_slot[r0 + threadIdx.x] - i * kr;
     const double uu = gram[((long long)i * kr + a) * kr + a];
@@ -324,6 +326,8 @@ hipError_t launch_calib_finalize(const double *gram, const int16_t *pos, const P
                                  int N, int kr, double lambda, double clip, double *part, float *S, float *L,
                                  float *h, double *pair_stats, hipStream_t s) {
   if (m > 0) {
+    // calib_pairs_kernel holds a tile's rows in LDS
+    if (bm < 1 || bm > kPairRows) return hipErrorInvalidValue;
     int NP = 64;
     while (NP < N) NP *= 2;
     calib_pairs_kernel<<<m * kr / bm + N, kPairThreads, 0, s>>>(gram, pos, pb.offsets, pb.tile_start0,

@@ -163,7 +163,8 @@ hipError_t launch_calib_routes(const int32_t *topk_ids, int m, int N, int K, int
 hipError_t launch_calib_gram(const float *Y, const int32_t *slot_row, int m, int kr, int d,
                              double *gram, hipStream_t s);
 // Pair sums per m-tile of the permutation pb (tile height bm, list tile_start0)
-// into part (calib_partial_doubles), then S, L and h.
+// into part (calib_partial_doubles), then S, L and h.  bm: 1 to 128
+// (hipErrorInvalidValue otherwise, before any launch).
 size_t calib_partial_doubles(int rows, int N, int bm);
 hipError_t launch_calib_finalize(const double *gram, const int16_t *pos, const PermBuffers &pb, int bm, int m,
                                  int N, int kr, double lambda, double clip, double *part, float *S, float *L,

@@ -6,6 +6,7 @@ import ctypes
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2608_24938_amd import exfold as X
 
@@ -130,3 +131,24 @@ def test_grids_cover_every_split(shape, rows, active):
         for p, cols, gate_up in ((gu, shape["inter"], True), (dn, shape["d"], False)):
             need = _tiles(p, sizes, cols, gate_up) + (256 if p["kind"] == WIDE else 0)
             assert p["grid"] >= need, (p, sizes)
+
+
+# The calibration's pair sums hold a gate/up tile's rows in LDS, 128 at most: every plan stays within that, and
+# the launch refuses a taller tile on the host.
+def test_gate_up_tiles_fit_the_pair_sums():
+    rng = np.random.default_rng(5)
+    for _ in range(4000):
+        d, inter, n = 128 * rng.integers(1, 65), 64 * rng.integers(1, 129), int(rng.integers(1, 257))
+        ly = layer(int(d), int(inter), n, 1, dtype=X.F32 if rng.random() < 0.2 else X.BF16)
+        gu, _ = plan(ly, int(np.exp(rng.uniform(0, np.log(1e6)))), n, int(rng.choice([64, 256, 304])))
+        assert 1 <= gu["bm"] <= 128
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="a host check: the call would launch if the check were missing")
+@pytest.mark.parametrize("bm", [129, 256])
+def test_pair_sums_refuse_a_taller_tile(bm):
+    fn = getattr(X.lib(), "_ZN6exfold21launch_calib_finalizeEPKdPKsRKNS_11PermBuffersEiiiiddPdPfS8_S8_S7_P12ihipStream_t")
+    i, f, v = ctypes.c_int, ctypes.c_double, ctypes.c_void_p
+    fn.argtypes, fn.restype = [v, v, v, i, i, i, i, f, f, v, v, v, v, v, v], i
+    buffers = (ctypes.c_void_p * 16)()
+    assert fn(None, None, ctypes.addressof(buffers), bm, 4, 8, 2, 0.0, 0.0, *[None] * 6) == 1  # hipErrorInvalidValue
