@@ -51,6 +51,19 @@ def test_calibration_at_tile_edges(n, k, m, mode):
     np.testing.assert_allclose(h.cpu().numpy(), rh, rtol=tol)
 
 
+SIMT, TILE, SKINNY, WIDE = range(4)
+
+
+def _plan(d, inter, n, k, T, shared=0, dtype=X.BF16):
+    """(kind, rows a tile, ranges of the reduction) of the gate/up and the down GEMM of moe_execute."""
+    out = (ctypes.c_int32 * 10)()
+    ly = X._Layer(d, inter, n, k, shared, dtype, 0, 0x10000, None, 0x10000, 0x10000, *[0x10000 if shared else None] * 2)
+    rows, active = T * k + (T if shared else 0), min(n, T * k) + (1 if shared else 0)
+    assert X.lib().exfold_gemm_plan(ctypes.byref(ly), rows, active, 256, out) == X.OK
+    direct = k == 1 and not shared  # one row a token: the down reduction is not split
+    return (out[0], out[1], out[3]), (out[5], out[6], 1 if direct else out[8])
+
+
 def _execute(shape, T, ids, seed):
     """moe_execute on given routes against the oracle: the largest per-token error."""
     lp = LayerPair(shape, seed=seed)
@@ -75,11 +88,14 @@ def _skewed(T, k, n, seed):
 # float32 tiles of 16, 32 and 64 rows: either side of 16 and 32 rows per busy expert, one
 # row, ragged groups, the shared expert, a reduction of one step a wave (d 128, I 64) and a
 # ragged last batch of steps (d 640: ten steps a wave; I 320: five).
-@pytest.mark.parametrize("d,inter,n,k,shared,T", [(128, 64, 5, 1, 0, 1), (128, 64, 5, 2, 0, 40), (128, 64, 5, 2, 0, 41),
-                                                  (640, 320, 5, 2, 320, 79), (640, 320, 5, 2, 0, 81),
-                                                  (256, 192, 3, 1, 192, 333), (1024, 576, 8, 2, 0, 1100)])
-def test_float32_tiles(d, inter, n, k, shared, T):
+@pytest.mark.parametrize("d,inter,n,k,shared,T,bm", [(128, 64, 5, 1, 0, 1, 16), (128, 64, 5, 2, 0, 40, 16),
+                                                     (128, 64, 5, 2, 0, 41, 32), (640, 320, 5, 2, 320, 64, 32),
+                                                     (640, 320, 5, 2, 320, 79, 64), (640, 320, 5, 2, 0, 80, 32),
+                                                     (640, 320, 5, 2, 0, 81, 64), (256, 192, 3, 1, 192, 333, 64),
+                                                     (1024, 576, 8, 2, 0, 1100, 64)])
+def test_float32_tiles(d, inter, n, k, shared, T, bm):
     shape = _shape(d, inter, n, k, shared=shared)
+    assert _plan(d, inter, n, k, T, shared, X.F32) == ((SIMT, bm, 1),) * 2
     assert _execute(shape, T, _skewed(T, k, n, T), seed=3) <= TOL_Y["f32"]
 
 
@@ -114,29 +130,45 @@ def test_wide_tile_edges(d, inter, k):
     ids = np.random.default_rng(d).permutation(np.repeat(np.arange(len(sizes)), sizes)).astype(np.int32)
     ids = ids.reshape(-1, k)
     shape = _shape(d, inter, len(sizes), k, dtype="bf16")
-    plan = (ctypes.c_int32 * 10)()
-    lp = X._Layer(d, inter, len(sizes), k, 0, X.BF16, 0, 0x10000, None, 0x10000, 0x10000, None, None)
-    assert X.lib().exfold_gemm_plan(ctypes.byref(lp), ids.size, len(sizes), 256, plan) == X.OK
-    assert plan[0] == 3 and plan[5] == (3 if d % 512 == 0 else 1)
+    gu, dn = _plan(d, inter, len(sizes), k, ids.shape[0])
+    assert gu[0] == WIDE and dn[0] == (WIDE if d % 512 == 0 else TILE)
     assert _execute(shape, ids.shape[0], ids, seed=4) <= TOL_Y["bf16"]
 
 
-# Skinny tiles of 32 and 64 rows (up to 12 and up to 24 gate/up or 48 down rows per busy expert) and
-# 64-row down tiles (up to 80): groups of 0, 1, 32, 33, 64, 65 and more rows; reductions that end
-# in half a 128-column stage (I = 192, 320, 704), of one stage (I = 128) and below one (I = 64); one and
-# several routes a token, the shared expert, a split down reduction (I = 4096; I = 1728 and 4160: ranges that end in half a stage).
-@pytest.mark.parametrize("d,inter,sizes,k,shared", [
-    (256, 192, [1, 0, 32, 33, 0, 2, 4, 0], 1, 0), (256, 192, [1, 0, 12, 33, 0, 24, 9, 1], 2, 192),
-    (128, 320, [64, 65, 0, 32, 33, 1, 3, 2], 1, 0), (384, 704, [64, 65, 0, 32, 33, 1, 3, 2], 2, 0),
-    (128, 128, [40, 30, 20, 60], 2, 128), (256, 64, [20, 10, 5, 1], 1, 0), (256, 64, [20, 10, 5, 1], 2, 0),
-    (256, 320, [64, 65, 63, 128, 129, 1], 2, 0), (640, 192, [64, 65, 63, 128, 20, 1], 1, 0),
-    (128, 4096, [3, 1, 0, 4], 2, 0), (128, 4160, [40, 50, 33, 65], 2, 0),
-    (512, 1728, [47] * 34, 2, 0),
+# Skinny tiles of 32 rows (gate/up up to 12 rows per busy expert, or 24 where there are at most four
+# tiles a CU), of 64 (gate/up up to 24, down up to 48) and 64-row down tiles (up to 80), each case with the
+# tiles it is there for: groups of 0, 1, 32, 33, 64, 65 and more rows; reductions that end in half a
+# 128-column stage (I = 192, 320, 704), of one stage (I = 128) and below one (I = 64); one and several
+# routes a token, the shared expert, a split down reduction (I = 4096; I = 1728 and 4160: ranges that end in
+# half a stage).
+_EDGES64 = [64, 65, 0, 33, 32, 1, 63, 2, 31, 0, 5, 0, 0, 0, 1, 0]
+
+
+@pytest.mark.parametrize("d,inter,sizes,k,shared,gu,dn", [
+    (256, 192, [1, 0, 32, 33, 0, 2, 4, 0], 1, 0, (SKINNY, 32, 1), (SKINNY, 32, 1)),
+    (256, 192, [1, 0, 12, 33, 0, 24, 9, 1], 2, 192, (SKINNY, 32, 1), (SKINNY, 32, 1)),
+    (128, 320, [64, 65, 0, 32, 33, 1, 3, 2], 1, 0, (TILE, 128, 1), (SKINNY, 64, 1)),
+    (384, 704, [64, 65, 0, 32, 33, 1, 3, 2], 2, 0, (TILE, 128, 1), (SKINNY, 64, 1)),
+    (128, 128, [40, 30, 20, 60], 2, 128, (TILE, 128, 1), (SKINNY, 64, 1)),
+    (256, 64, [20, 10, 5, 1], 1, 0, (SKINNY, 32, 1), (TILE, 64, 1)),
+    (256, 64, [20, 10, 5, 1], 2, 0, (SKINNY, 32, 1), (TILE, 64, 1)),
+    (256, 320, [64, 65, 63, 128, 129, 1], 2, 0, (TILE, 128, 1), (TILE, 64, 1)),
+    (640, 192, [64, 65, 63, 128, 20, 1], 1, 0, (TILE, 128, 1), (TILE, 64, 1)),
+    (128, 4096, [3, 1, 0, 4], 2, 0, (SKINNY, 32, 1), (SKINNY, 32, 4)),
+    (128, 4160, [40, 50, 33, 65], 2, 0, (TILE, 128, 1), (SKINNY, 64, 5)),
+    (512, 1728, [47] * 34, 2, 0, (TILE, 128, 1), (SKINNY, 64, 3)),
+    # 64-row gate/up tiles (more than four 32-column tiles a CU): one stage of d, three, the shared expert
+    (128, 2112, _EDGES64, 1, 0, (SKINNY, 64, 1), (SKINNY, 32, 1)),
+    (384, 2112, _EDGES64, 2, 0, (SKINNY, 64, 1), (SKINNY, 32, 3)),
+    (256, 2048, _EDGES64 + [10] * 16, 2, 2048, (SKINNY, 64, 1), (SKINNY, 32, 2)),
     # more than two 128-column down tiles a CU: 64-row tiles from 21 rows on average, skinny at 20
-    (2048, 128, [21] * 33, 1, 0), (2048, 192, [20] * 33, 1, 0), (4096, 64, [64, 1, 0, 65, 33] * 7, 2, 0)])
-def test_streaming_tile_edges(d, inter, sizes, k, shared):
+    (2048, 128, [21] * 33, 1, 0, (SKINNY, 32, 1), (TILE, 64, 1)),
+    (2048, 192, [20] * 33, 1, 0, (SKINNY, 32, 1), (SKINNY, 64, 1)),
+    (4096, 64, [64, 1, 0, 65, 33] * 7, 2, 0, (TILE, 128, 1), (TILE, 64, 1))])
+def test_streaming_tile_edges(d, inter, sizes, k, shared, gu, dn):
     ids = np.random.default_rng(inter).permutation(np.repeat(np.arange(len(sizes)), sizes)).astype(np.int32)
     ids = ids[: len(ids) // k * k].reshape(-1, k)
+    assert _plan(d, inter, len(sizes), k, ids.shape[0], shared) == (gu, dn)
     shape = _shape(d, inter, len(sizes), k, dtype="bf16", shared=shared)
     assert _execute(shape, ids.shape[0], ids, seed=5) <= TOL_Y["bf16"]
 

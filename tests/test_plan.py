@@ -11,7 +11,7 @@ import torch
 from paper_2608_24938_amd import exfold as X
 
 FAKE = 0x10000  # weights are never dereferenced by the planner
-SIMT, TILE, SKINNY, WIDE = range(4)
+SIMT, TILE, SKINNY, WIDE = range(4)  # SIMT: the float32 layers
 
 
 def layer(d, inter, n, k, shared=0, dtype=X.BF16):
@@ -77,9 +77,27 @@ def test_skinny_tile_height(shape, rows, active, gu_bm, dn_bm):
     assert (gu["bm"], dn["bm"]) == (gu_bm, dn_bm), (gu, dn)
 
 
-def test_float32_layers_take_the_simt_kernels():
-    gu, dn = plan(layer(256, 512, 8, 2, dtype=X.F32), 64, 8)
-    assert gu["kind"] == dn["kind"] == SIMT
+# Down tiles: skinny up to 48 rows a busy expert, or 20 where there are more than two 128-column tiles a CU, and
+# never for a reduction below one skinny stage (I = 64); else 128 columns, 64 rows a tile up to 80.  Gate/up:
+# skinny up to 24 rows.
+@pytest.mark.parametrize("d,inter,active,rows,gu,dn", [
+    (2048, 768, 32, 24 * 32, (SKINNY, 32), (SKINNY, 32)), (2048, 768, 32, 24 * 32 + 1, (TILE, 128), (SKINNY, 64)),
+    (2048, 768, 32, 48 * 32, (TILE, 128), (SKINNY, 64)), (2048, 768, 32, 48 * 32 + 1, (TILE, 128), (TILE, 64)),
+    (2048, 768, 32, 80 * 32, (TILE, 128), (TILE, 64)), (2048, 768, 32, 80 * 32 + 1, (TILE, 128), (TILE, 128)),
+    (2048, 768, 33, 20 * 33, (SKINNY, 32), (SKINNY, 64)), (2048, 768, 33, 20 * 33 + 1, (SKINNY, 32), (TILE, 64)),
+    (256, 64, 4, 4, (SKINNY, 32), (TILE, 64)), (256, 64, 4, 80 * 4 + 1, (TILE, 128), (TILE, 128)),
+    (256, 192, 4, 48 * 4, (TILE, 128), (SKINNY, 64)), (256, 192, 4, 48 * 4 + 1, (TILE, 128), (TILE, 64)),
+])
+def test_down_tile(d, inter, active, rows, gu, dn):
+    a, b = plan(layer(d, inter, active, 1), rows, active)
+    assert ((a["kind"], a["bm"]), (b["kind"], b["bm"])) == (gu, dn), (a, b)
+
+
+@pytest.mark.parametrize("rows,bm", [(1, 16), (16 * 8, 16), (16 * 8 + 1, 32), (32 * 8, 32), (32 * 8 + 1, 64), (9000, 64)])
+def test_float32_tile_height(rows, bm):
+    gu, dn = plan(layer(256, 512, 8, 2, dtype=X.F32), rows, 8)
+    assert gu["kind"] == dn["kind"] == SIMT and gu["bm"] == dn["bm"] == bm
+    assert gu["ksplit"] == dn["ksplit"] == 1  # the float32 kernel adds no partials
 
 
 def test_query_validation():
@@ -96,8 +114,6 @@ def test_query_validation():
 
 def _tiles(p, sizes, out_cols, gate_up):
     """Tiles the device-side list holds for these group sizes under plan p."""
-    if p["kind"] == SIMT:
-        return 0
     n_tiles = out_cols // (p["bn"] // 2 if gate_up else p["bn"])
     if p["kind"] == WIDE:       # 128-row units, one tile per unit and pair of n-tiles
         return int(sum(-(-r // 128) for r in sizes)) * (n_tiles // 2)
@@ -120,6 +136,9 @@ def _splits(rows, groups, rng):
     (MIXTRAL, 4096, 8), (MIXTRAL, 20000, 8), (MIXTRAL, 64, 4), (QWEN3, 32768, 128), (QWEN3, 1024, 16),
     (GLM, 4096 * 4 + 4096, 129), (GLM, 64 * 8 + 64, 33),
     (dict(d=384, inter=256, n=8, k=2), 8192, 8), (dict(d=2048, inter=1024, n=8, k=2), 9000, 8),
+    (dict(d=1024, inter=2112, n=24, k=3), 400, 24), (dict(d=7168, inter=4160, n=8, k=2), 16, 2),
+    (dict(d=256, inter=512, n=8, k=2, dtype=X.F32), 64, 8), (dict(d=640, inter=320, n=5, k=2, dtype=X.F32), 161, 5),
+    (dict(d=128, inter=64, n=60, k=4, dtype=X.F32), 1200, 60),
 ])
 def test_grids_cover_every_split(shape, rows, active):
     ly = layer(**shape)
