@@ -333,7 +333,8 @@ const char *exfold_status_str(exfold_status status);
 
 /* Kernel families of the expert GEMMs (exfold_gemm_plan). */
 enum {
-  EXFOLD_GEMM_SIMT = 0,    /* float32 layers                                          */
+  EXFOLD_GEMM_SIMT = 0,    /* float32 layers (MFMA tiles of 16, 32 or 64 rows; the
+                              name is that of the scalar kernels they replaced)       */
   EXFOLD_GEMM_TILE = 1,    /* MFMA tiles of 128 columns, 64 or 128 rows               */
   EXFOLD_GEMM_SKINNY = 2,  /* 32x64 and 64x64 tiles streaming weights (few rows per
                               expert)                                                 */

@@ -58,7 +58,8 @@ constexpr int kBK = 64;
 // no hint 256, on every weight row 266, on single m-tiles 235).  It loses only where
 // the weights fit the last-level cache and nothing else runs between two calls (32
 // experts, d 1024, I 512, 300 tokens x 4, skewed: 46.1 -> 48.2 us; with 2 GB of other
-// layers between them 50.8 -> 48.3).
+// layers between them 50.8 -> 48.3; the most seen: d 2048, I 1408, 4 tokens x 6 on 64
+// skewed experts, 56.4 -> 62.4, and 66.5 -> 59.0 with 5 GB of other layers).
 template <bool ONCE>
 __device__ __forceinline__ u32x4 load_w16(const bf16_t *p) {
   if constexpr (ONCE)
@@ -351,10 +352,13 @@ __global__ __launch_bounds__(256, 1) void expert_gemm_tile(const GemmKArgs p) {
 // straight into LDS (global_load_lds_dwordx4) through a ring of reduction
 // stages: no staging registers and no LDS write instructions.  Against 128x128
 // tiles the bytes loaded per flop halve, and the weight panel a tile shares
-// with the other m-tiles of its expert is fetched from HBM about once (2.4 GB
-// per Mixtral-shaped launch against 3.8-5 GB).  Measured on that launch, the
-// 64-wide stages with two ring buffers beat 32-wide stages with four or five
-// buffers (more bytes in flight, but 64-byte row pieces and twice the barriers).
+// with the other m-tiles of its expert is fetched from HBM fewer times: a
+// Mixtral-shaped launch reads 3.0-3.1 GB, 2.0 GB of them needed, against 3.8-5
+// GB (2.4 GB with one barrier a stage, one stage ahead: tiles whose loads run 1.5
+// stages ahead drift further apart, at less time all the same).  Measured with one
+// barrier a stage, the 64-wide stages with two ring buffers beat 32-wide stages
+// with four or five buffers (more bytes in flight, but 64-byte row pieces and
+// twice the barriers).
 // ---------------------------------------------------------------------------
 constexpr int kWide = 256, kWideWaves = 8, kWideBK = 64;
 
@@ -450,17 +454,18 @@ constexpr int kWideSmemElems = 2 * (kWide / 2 + 2 * kWideBN) * kWideBK;
 // last phase do not use the weight half that it reads for the next stage, and
 // no MFMA precedes the first phase.  The reads are a block of MFMAs old by then,
 // so the wait costs nothing: Qwen3-shaped prefill 461 us a layer without it, 464
-// with it, on two boxes.)  Before the phase's barrier tile p + 2 must have landed:
+// with it, on two cards.)  Before the phase's barrier tile p + 2 must have landed:
 // at most five tiles, 10 loads, stay in flight; a load has six phases (1.5
 // stages) to land.  Tail tiles: five tiles a stage on four phases (the second
 // issues two), six or seven stay in flight.
 //
 // One barrier a stage with every wave reading, loading and multiplying at once
-// (one stage ahead) kept the MFMA pipes busy 57% of the cycles, this 72% of them
-// at 11% lower clock (the launch is held by the chip's power): 4096 rows on 8
-// Mixtral-shaped experts, 512 each, gate/up 877 -> 842 us (1143 TFLOP/s),
-// down 437 -> 415; ragged groups gain most, in their tail tiles (8192 Qwen3-shaped
-// tokens, K' = 4: 247 -> 229 and 177 -> 156 us).
+// (one stage ahead) kept the MFMA pipes busy 57% of the cycles at 1.88 GHz on a
+// Mixtral-shaped gate/up launch of ragged groups, this 66-67% at 1.76 and 1.67 GHz
+// (two cards: the launch is held by the chip's power); 4096 rows on 8 such
+// experts, 512 each, gate/up 877 -> 842 us (1143 TFLOP/s), down 437 -> 415.  Ragged
+// groups gain most, in their tail tiles (8192 Qwen3-shaped tokens, K' = 4: 247 ->
+// 229 and 177 -> 156 us; pipes busy 47.5 -> 52% and 36 -> 40%).
 //
 // TMV: 32-row blocks of the wave that hold rows of the group (full: 2 .. 4, tail:
 // 0 .. 2; the others' fragments are not read and their MFMAs not issued).
@@ -923,9 +928,9 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void expert_down_wide(const Gem
 }
 
 // Block (r, c): remainder tile r, tile rows 16 c .. 16 c + 15, sixteen threads
-// a row.  Gate/up: H columns 128 nt + col from the gate and up partials laid
-// out as the accumulators of the waves (wide_store_partial); down: the 256
-// (tail tile: 512) output columns scaled by the row's routing weight.
+// a row.  The partial tiles are row-major, 256 (tail tile: 512) columns a row.
+// Gate/up: H column 128 nt + col from the gate column and the up column 128
+// further; down: the output columns scaled by the row's routing weight.
 template <bool GATE_UP, bool DIRECT>
 __global__ __launch_bounds__(256) void expert_wide_fixup(const GemmKArgs p, int G) {
   const WideSplit w = wide_split(p, G);
