@@ -293,8 +293,8 @@ size_t exfold_execute_workspace_size(const exfold_layer *layer, int64_t T, int64
 
 /*
  * Execute given route metadata (the expert stage that the fold feeds, Eq.
- * moe_output on arbitrary routes): route_ids/route_w [T, K_out] (ids in [0, N),
- * duplicates allowed, any weights).  y as in exfold_moe_forward.  debug may be
+ * moe_output on arbitrary routes): route_ids/route_w [T, K_out] (1 <= K_out <= 1024,
+ * ids in [0, N), duplicates allowed, any weights).  y as in exfold_moe_forward.  debug may be
  * NULL; only its offsets/row_slot members are used.
  */
 exfold_status exfold_moe_execute(const exfold_layer *layer, const void *x, int64_t T,

@@ -1638,9 +1638,45 @@ __global__ __launch_bounds__(256) void combine_kernel(const InT *__restrict__ Y,
   }
 }
 
+// The same sums for more rows a token than the registers of combine_kernel hold (only
+// exfold_moe_execute takes more than 16 routes): the row indices are read as the rows are.
+template <typename InT, typename OutT>
+__global__ __launch_bounds__(256) void combine_many_kernel(const InT *__restrict__ Y, int ksplit, int rows,
+                                                          const int32_t *__restrict__ slot_row,
+                                                          const float *__restrict__ row_w, int k_out, int d,
+                                                          int shared_base, OutT *__restrict__ y) {
+  const int i = blockIdx.x, c = (blockIdx.y * 256 + threadIdx.x) * 4;
+  if (c >= d) return;
+  const int nr = k_out + (shared_base >= 0 ? 1 : 0);
+  constexpr bool kScale = sizeof(InT) == 2;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int sp = 0; sp < ksplit; ++sp) {
+    const InT *base = Y + (long long)sp * rows * d + c;
+#pragma unroll 4
+    for (int k = 0; k < nr; ++k) {
+      const int r = k < k_out ? slot_row[(long long)i * k_out + k] : shared_base + i;
+      const float w = kScale ? row_w[r] : 1.f;
+      float v[4];
+      load_cols<InT, 4>(base + (long long)r * d, v);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q] = kScale ? fmaf(w, v[q], acc[q]) : acc[q] + v[q];
+    }
+  }
+  OutT *o = y + (long long)i * d + c;
+  if constexpr (sizeof(OutT) == 2)
+    store4_bf16(reinterpret_cast<bf16_t *>(o), acc[0], acc[1], acc[2], acc[3]);
+  else
+    *reinterpret_cast<float4 *>(o) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+}
+
 template <typename InT, typename OutT>
 static void launch_combine_t(const InT *Y, int ksplit, int rows, const int32_t *slot_row, const float *row_w,
                              int T, int k_out, int d, int shared_base, OutT *y, hipStream_t s) {
+  if (k_out + (shared_base >= 0 ? 1 : 0) > kMaxTopK + 1) {
+    combine_many_kernel<InT, OutT><<<dim3(T, (d + 1023) / 1024), 256, 0, s>>>(Y, ksplit, rows, slot_row, row_w, k_out,
+                                                                              d, shared_base, y);
+    return;
+  }
   // eight columns a thread once the grid covers the CUs a few times over; four below
   if ((long long)T * d >= 256LL * 256 * 8 * 4) {
     const dim3 grid(T, (d + 2047) / 2048);

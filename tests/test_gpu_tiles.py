@@ -99,6 +99,18 @@ def test_float32_tiles(d, inter, n, k, shared, T, bm):
     assert _execute(shape, T, _skewed(T, k, n, T), seed=3) <= TOL_Y["f32"]
 
 
+# More routes a token than the combine holds in registers (17 rows, the shared one among them): either side
+# of that, bf16 rows and split float32 partials (I = 4096), a ragged last step of four.
+@pytest.mark.parametrize("d,inter,n,k,shared,T,dtype", [
+    (256, 64, 5, 16, 64, 3, "bf16"), (256, 64, 5, 17, 0, 3, "bf16"), (256, 64, 5, 17, 64, 3, "bf16"),
+    (256, 64, 24, 18, 0, 9, "f32"), (1152, 192, 40, 33, 192, 7, "bf16"), (128, 4096, 4, 19, 0, 2, "bf16"),
+    (128, 64, 256, 300, 0, 2, "f32")])
+def test_execute_of_many_routes(d, inter, n, k, shared, T, dtype):
+    ids = np.random.default_rng(k).integers(0, n, size=(T, k)).astype(np.int32)
+    shape = _shape(d, inter, n, min(k, n, 16), dtype=dtype, shared=shared)
+    assert _execute(shape, T, ids, seed=6) <= TOL_Y[dtype]
+
+
 # float32 router: N <= 32 in the routing kernel up to 1024 tokens (8, 16 and 32 experts a
 # build), 16 x 16 tiles beyond either limit.
 @pytest.mark.parametrize("n,T,d", [(7, 1, 128), (13, 5, 1152), (32, 33, 640), (33, 17, 384), (32, 1024, 128),
